@@ -52,7 +52,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E peak (published)
 MAIN_KERNELS = {"conv3d_bf16": ("conv3d_bf16",), "head": ("conv_head",),
                 "tap1x1": ("conv_tap1x1", "conv_tap1x1_chunk"),
                 "pointwise": ("pointwise_conv", "pointwise_resident"),
-                "fast_f32": ("fast_conv3d",), "fallback_direct": ("fallback_conv3d",)}
+                "fast_f32": ("fast_conv3d",), "fallback_direct": ("fallback_conv3d", "fallback_mfma")}
 MAIN_SYMBOLS = tuple(n for names in MAIN_KERNELS.values() for n in names)
 AUX_KERNELS = ("splitk_reduce", "cache_copy", "cache_copy_pro", "prologue_pass")
 

@@ -129,6 +129,13 @@ hipError_t launch_fast_tap1x1(const Geo& g, const void* x, const void* cache, co
 hipError_t launch_fallback(const Geo& g, const void* x, const void* cache, const void* w,
                            const void* bias, void* y, hipStream_t s, const Fuse& fu = Fuse{},
                            LaunchInfo* info = nullptr);
+// fallback, bf16 / fp16 on matrix cores (fallback_mfma.hip).  False: the call
+// does not fit that kernel's tile (nothing launched, *err = hipSuccess) and
+// takes the direct kernel; true: launched, or described in *info, *err the
+// launch's status.
+bool launch_fallback_mfma(const Geo& g, const void* x, const void* cache, const void* w,
+                          const void* bias, void* y, hipStream_t s, const Fuse& fu,
+                          LaunchInfo* info, hipError_t* err);
 // the fused form's prologue as its own pass: u = RNE_bf16(SiLU(x * scale +
 // shift)) over the whole new chunk (fallback.hip)
 hipError_t launch_prologue(const Geo& g, const void* x, const float* scale, const float* shift,

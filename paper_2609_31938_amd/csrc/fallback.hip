@@ -5,7 +5,9 @@
 // unsupported calls to the original Conv3D, Alg. 1): any kernel size, stride,
 // dilation, groups, padding (including a negative effective left pad and a
 // right pad), and bf16 / fp16 / fp32 storage, accumulating in fp32.  Pointwise
-// (1x1x1) bf16 / fp16 calls go to the matrix-core kernel in pointwise.hip.
+// (1x1x1) bf16 / fp16 calls go to the matrix-core kernel in pointwise.hip,
+// other bf16 / fp16 calls to the one in fallback_mfma.hip; the direct kernel
+// here keeps fp32 and the shapes whose windows do not fit that kernel's tile.
 #include "c3c_internal.h"
 #include "fuse_dev.h"
 
@@ -346,6 +348,8 @@ hipError_t launch_fallback(const Geo& g, const void* x, const void* cache, const
       (fu.residual == nullptr || (reinterpret_cast<uintptr_t>(fu.residual) & 7) == 0))
     return launch_pointwise(g, x, cache, w, bias, y, s, fu, info);
   if (g.d.dtype == C3C_DTYPE_F32) return launch_fb<float>(g, x, cache, w, bias, y, s, fu, info);
+  hipError_t e;
+  if (launch_fallback_mfma(g, x, cache, w, bias, y, s, fu, info, &e)) return e;
   return launch_fb<uint16_t>(g, x, cache, w, bias, y, s, fu, info);
 }
 

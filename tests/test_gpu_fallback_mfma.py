@@ -1,0 +1,132 @@
+"""GPU parity of the matrix-core fallback kernel (bf16 / f16 direct Conv3D)
+against the oracle, at the sizes where its tiling can go wrong: remainders of
+a 32-wide K stage, K chunks that split a channel's taps, every output-channel
+tile, one and several fragment columns, odd widths, tensors at odd element
+addresses, groups of few channels, frames outside Z.
+
+Bar: bf16 outputs carry one rounding (2^-9 relative) and fp32 sums, f16
+outputs 2^-12; max|err| / max|ref| <= 1e-2 and 2e-3 leave room for the
+rounding of the largest values only.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_31938_amd import c3c
+from paper_2609_31938_amd.inputs import spec
+
+from gpu_util import as_f64, chunk, guarded, guards_intact, layer, metrics, oracle_args, say
+
+pytestmark = pytest.mark.gpu
+
+BAR = {"bf16": 1e-2, "f16": 2e-3}
+FORCE = c3c.MODE_FORCE_FALLBACK
+
+
+def _odd(t):
+    """The same values at an odd element address (2-byte alignment only)."""
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    buf[1:] = t.flatten()
+    return buf[1:].view(t.shape)
+
+
+def _run(sp, dtype, mode, odd=False, poison=None):
+    plan = c3c.plan_query(c3c.Context(mode), sp, dtype)
+    say(f"fallback case {dtype} {sp} odd={odd} plan={plan}")
+    assert plan["kernel"] == "fallback_direct", plan
+    ctx = c3c.Context(mode)
+    w, b = layer(sp, dtype, 913)
+    x = chunk(sp, dtype, 913, 0, 0)
+    cache = chunk(dict(sp, T=sp["Tc"]), dtype, 913, 0, 1) if sp["Tc"] else None
+    if poison is not None:
+        x[poison] = float("inf")
+    if odd:
+        w, x, cache = _odd(w), _odd(x), None if cache is None else _odd(cache)
+    To, Ho, Wo, L = c3c.output_dims(sp, dtype)
+    y, ybuf = guarded((sp["N"], sp["Co"], To, Ho, Wo), dtype)
+    y, _ = c3c.conv3d_causal_cached(ctx, sp, x, cache, w, None, b, y, None)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf), "a write outside the output"
+    ref = oracle.conv3d(sp, dtype, *oracle_args(sp, x, cache, w, b))
+    return plan, as_f64(y), ref
+
+
+CASES = [
+    # K = 9 Ci: one partial stage, several chunks and a partial last one
+    ("f16", dict(Ci=3, Co=16, T=2, H=11, W=40, Kt=1, s_h=2, s_w=2), 0),
+    ("bf16", dict(Ci=37, Co=32, T=1, H=30, W=72, Kt=1, s_h=2, s_w=2), 0),
+    ("f16", dict(Ci=100, Co=70, T=2, H=17, W=129, Kt=1, s_h=2, s_w=2), 0),
+    # 75 taps: a K chunk starts and ends inside a channel's taps
+    ("bf16", dict(Ci=21, Co=33, T=3, Tc=2, H=12, W=50, Kt=3, Kh=5, Kw=5, s_h=2), 0),
+    # fragment columns: a tall narrow and a flat wide plane
+    ("bf16", dict(Ci=20, Co=20, T=1, H=70, W=14, Kt=1, s_h=2, s_w=1), 0),
+    ("f16", dict(Ci=20, Co=20, T=1, H=3, W=260, Kt=1, s_h=2, s_w=1), 0),
+    # three taps in time with frames outside Z on both sides, dilation, stride
+    ("f16", dict(N=2, Ci=12, Co=24, T=3, Tc=1, H=9, W=31, p_r=1), 0),
+    ("bf16", dict(Ci=12, Co=24, T=5, Tc=3, H=9, W=31, s_t=2, d_t=2, p_base=4, p_r=2), 0),
+    ("f16", dict(Ci=9, Co=10, T=2, Tc=2, H=20, W=33, d_h=3, d_w=2, p_h=3, p_w=2, s_w=2), 0),
+    # groups: one and three channels a group
+    ("bf16", dict(Ci=16, Co=16, T=3, Tc=2, H=10, W=20, groups=16), 0),
+    ("f16", dict(Ci=12, Co=36, T=2, H=10, W=20, Kt=1, groups=4), 0),
+    # a 3x3 call forced off the fast route
+    ("bf16", dict(Ci=64, Co=48, T=2, Tc=2, H=13, W=45), FORCE),
+    # padding wider than a segment
+    ("bf16", dict(Ci=8, Co=8, T=1, H=6, W=10, Kt=1, Kh=7, Kw=19, p_h=3, p_w=9, s_h=2), 0),
+]
+
+
+@pytest.mark.parametrize("dtype,over,mode", CASES)
+@pytest.mark.parametrize("odd", [False, True])
+def test_matrix_core_fallback_matches_oracle(dtype, over, mode, odd):
+    plan, got, ref = _run(spec(**over), dtype, mode, odd)
+    assert plan["tile_h"] > 0, plan  # the matrix-core kernel (the direct one tiles the flat plane)
+    m = metrics(got, ref)
+    assert m["nonfinite"] == 0 and m["rel"] <= BAR[dtype], m
+
+
+@pytest.mark.parametrize("Co,tile", [(192, 192), (190, 192), (120, 128), (96, 96), (90, 96), (64, 64),
+                                     (60, 64), (32, 32), (30, 32), (16, 16)])
+def test_every_output_channel_tile(Co, tile):
+    """Calls large enough to take each tile, exact and with a remainder."""
+    even = Co % 32 == 0 or Co == 16
+    over = dict(Ci=6, Co=Co, T=4, H=160 if even else 161, W=400 if even else 401, Kt=1, s_h=2, s_w=2)
+    plan, got, ref = _run(spec(**over), "f16" if even else "bf16", 0)
+    assert plan["tile_co"] == tile, plan
+    m = metrics(got, ref)
+    assert m["nonfinite"] == 0 and m["rel"] <= BAR["f16" if even else "bf16"], m
+
+
+@pytest.mark.parametrize("dtype,over", [
+    ("bf16", dict(Ci=8, Co=8, T=1, H=200, W=300, Kt=1, s_h=40, s_w=40, p_h=1)),  # windows past LDS
+    ("f32", dict(Ci=16, Co=24, T=2, H=20, W=31, Kt=1, s_h=2, s_w=2)),
+])
+def test_direct_kernel_keeps_the_rest(dtype, over):
+    plan, got, ref = _run(spec(**over), dtype, 0)
+    assert plan["tile_h"] == 0, plan
+    m = metrics(got, ref)
+    assert m["nonfinite"] == 0 and m["rel"] <= (1e-5 if dtype == "f32" else BAR[dtype]), m
+
+
+@pytest.mark.parametrize("dtype,Ci", [("bf16", 5), ("f16", 35), ("bf16", 64)])
+def test_infinity_stays_in_its_receptive_field(dtype, Ci):
+    """A K stage's padding (past the last channel, past the row of w) and the
+    image's border multiply nothing: only outputs that read the infinite
+    input are not finite."""
+    sp = spec(Ci=Ci, Co=20, T=1, H=21, W=45, Kt=1, s_h=2, s_w=2)
+    _, got, ref = _run(sp, dtype, 0, poison=(0, Ci - 1, 0, 8, 13))
+    assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+    ok = np.isfinite(ref)
+    assert metrics(got[ok], ref[ok])["rel"] <= BAR[dtype]
+
+
+def test_subnormal_f16_inputs():
+    """Subnormal halves are products like any other (no flush to zero)."""
+    sp = spec(Ci=32, Co=16, T=1, H=8, W=16, Kt=1, s_h=2, s_w=2, has_bias=0)
+    w = torch.full((16, 32, 1, 3, 3), 256.0, dtype=torch.float16, device="cuda")
+    x = torch.full((1, 32, 1, 8, 16), 2.0 ** -20, dtype=torch.float16, device="cuda")
+    say("fallback case f16 subnormal inputs")
+    y, _ = c3c.conv3d_causal_cached(c3c.Context(), sp, x, None, w, None, None)
+    torch.cuda.synchronize()
+    # interior outputs: 9 * 32 products of 2^8 * 2^-20
+    assert y[0, :, 0, 1:-1, 1:-1].eq(9 * 32 * 2.0 ** -12).all()
