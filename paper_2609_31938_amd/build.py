@@ -18,7 +18,7 @@ LIB = os.path.join(HERE, "libc3c.so")
 BUILD = os.path.join(ROOT, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["c3c_host.cpp", "fast_conv.hip", "conv_bf16.hip", "conv_tap1x1.hip", "conv_head.hip",
+SOURCES = ["c3c_host.cpp", "fast_conv.hip", "conv_bf16.hip", "conv_f32.hip", "conv_tap1x1.hip", "conv_head.hip",
            "fallback.hip", "fallback_mfma.hip", "pointwise.hip", "mfma_probe.hip", "noalloc.hip", "norm.hip"]
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

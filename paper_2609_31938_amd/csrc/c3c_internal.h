@@ -84,6 +84,11 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
                             const void* bias, void* y, void* cache_out, void* ws,
                             int64_t ws_bytes, bool* cache_written, hipStream_t s,
                             const Fuse& fu = Fuse{}, LaunchInfo* info = nullptr);
+// fp32 fast kernel, 3x3 and 1x1 (conv_f32.hip); writes cache_out itself when
+// it can (*cache_written), else the caller copies the cache
+hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const void* wpack,
+                           const void* bias, void* y, void* cache_out, bool* cache_written,
+                           hipStream_t s, LaunchInfo* info = nullptr);
 // fp32 partial-sum bytes a bf16 fast call would split into (0: it runs unsplit)
 int64_t fast_bf16_workspace_bytes(const Geo& g);
 // fallback, pointwise case (pointwise.hip): 1x1x1, unit spatial stride, no

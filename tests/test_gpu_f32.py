@@ -1,0 +1,79 @@
+"""GPU parity of the fp32 kernel against the oracle where its tiling can go
+wrong: narrow, flat and odd frames (the tile's shape follows the frame),
+channel counts around a stage (16 channels; 32 for 1x1), odd channel pairs,
+ragged output-channel tiles, both wave splits, frames outside Z, the cache
+written by the kernel and by the copy.
+
+Bar: fp32 sums of up to 27 * 96 products of unit-variance terms: rounding
+errors add up to about sqrt(K) * 2^-24 of the result's scale, 3e-6 here;
+max|err| / max|ref| <= 1e-5.  The cache is bit-exact.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_31938_amd import c3c
+from paper_2609_31938_amd.inputs import spec
+
+from gpu_util import as_f64, chunk, guarded, guards_intact, host, layer, metrics, oracle_args, say
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    dict(Ci=16, Co=32, T=2, Tc=2, H=32, W=32),
+    dict(Ci=15, Co=33, T=2, Tc=2, H=9, W=1),
+    dict(Ci=17, Co=31, T=1, Tc=0, H=200, W=1),
+    dict(Ci=1, Co=1, T=1, Tc=2, H=1, W=7),
+    dict(Ci=33, Co=64, T=2, Tc=1, H=1, W=300),
+    dict(Ci=32, Co=40, T=3, Tc=2, H=2, W=129),
+    dict(Ci=18, Co=20, T=2, Tc=3, H=13, W=85),            # p_l < 0
+    dict(N=2, Ci=31, Co=65, T=2, Tc=2, H=23, W=43),
+    dict(Ci=24, Co=96, T=4, Tc=2, H=60, W=104),            # more than two workgroups a compute unit
+    dict(Ci=20, Co=16, T=5, Tc=4, H=6, W=40, d_t=2, p_base=4),
+    dict(Ci=20, Co=36, T=2, Tc=2, H=7, W=9, Kt=5, p_base=4),
+    dict(Ci=12, Co=20, T=3, Tc=2, H=6, W=35, p_r=1),
+    dict(Ci=19, Co=20, T=3, H=6, W=35, Kt=1),              # one temporal tap: no cache
+    # 1x1: the plane as one row, temporal strides (the copy writes the cache)
+    dict(Ci=31, Co=33, T=3, Tc=2, H=5, W=7, Kh=1, Kw=1),
+    dict(Ci=64, Co=32, T=2, Tc=2, H=11, W=129, Kh=1, Kw=1),
+    dict(Ci=33, Co=96, T=9, Tc=1, H=40, W=104, Kh=1, Kw=1, s_t=2, p_base=1),
+    dict(Ci=70, Co=40, T=6, Tc=0, H=8, W=16, Kh=1, Kw=1, s_t=3),
+]
+
+
+@pytest.mark.parametrize("over", CASES)
+def test_f32_kernel_matches_oracle(over):
+    sp = spec(**over)
+    ctx = c3c.Context(c3c.MODE_STRICT)
+    plan = c3c.plan_query(ctx, sp, "f32")
+    say(f"f32 case {sp} plan={plan}")
+    assert plan["kernel"] == "fast_f32"
+    w, b = layer(sp, "f32", 915)
+    x = chunk(sp, "f32", 915, 0, 0)
+    cache = chunk(dict(sp, T=sp["Tc"]), "f32", 915, 0, 1) if sp["Tc"] else None
+    To, Ho, Wo, L = c3c.output_dims(sp, "f32")
+    y, ybuf = guarded((sp["N"], sp["Co"], To, Ho, Wo), "f32")
+    co, cbuf = guarded((sp["N"], sp["Ci"], L, sp["H"], sp["W"]), "f32")
+    c3c.conv3d_causal_cached(ctx, sp, x, cache, w, c3c.weight_repack(ctx, sp, w), b, y, co)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf) and guards_intact(cbuf), "a write outside the outputs"
+    args = oracle_args(sp, x, cache, w, b)
+    m = metrics(as_f64(y), oracle.conv3d(sp, "f32", *args))
+    assert m["nonfinite"] == 0 and m["rel"] <= 1e-5, m
+    assert np.array_equal(host(co).numpy(), oracle.cache_update(sp, "f32", args[0], args[1]))
+
+
+@pytest.mark.parametrize("over", [dict(Ci=17, Co=20, H=9, W=21), dict(Ci=35, Co=20, H=9, W=21, Kh=1, Kw=1)])
+def test_infinity_stays_in_its_receptive_field(over):
+    """Padding -- channel pairs past the last, lanes past the tile -- multiplies nothing."""
+    sp = spec(T=2, Tc=2, **over)
+    say(f"f32 case {sp} with an infinite input")
+    ctx = c3c.Context(c3c.MODE_STRICT)
+    w, b = layer(sp, "f32", 915)
+    x, cache = chunk(sp, "f32", 915, 0, 0), chunk(sp, "f32", 915, 0, 1)
+    x[0, sp["Ci"] - 1, 1, 4, 8] = float("inf")
+    y, _ = c3c.conv3d_causal_cached(ctx, sp, x, cache, w, c3c.weight_repack(ctx, sp, w), b)
+    torch.cuda.synchronize()
+    ref = oracle.conv3d(sp, "f32", *oracle_args(sp, x, cache, w, b))
+    assert np.array_equal(np.isfinite(as_f64(y)), np.isfinite(ref))
