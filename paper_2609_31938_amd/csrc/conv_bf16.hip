@@ -191,6 +191,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
     __amdgpu_buffer_rsrc_t rs;
     uint32_t cs;     // bytes between channel planes of the source
     uint32_t wbase;
+    uint32_t par;    // unaligned form: elements from the resource's base to the source (0 or 1)
     int k, c0, f;
   };
   auto stage_at = [&](int ki, int chunk) {
@@ -207,6 +208,15 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
     int64_t bytes = ((a.Ci - 1 - st.c0) * cstride + a.hw) * 2;
     bytes = bytes > 0x7fffffff ? 0x7fffffff : bytes;
     bytes = bytes < 0 ? 0 : bytes;
+    st.par = 0;
+    if (!ALIGNED) {
+      // dword-aligned base and size (the dword of the last element included)
+      st.par = static_cast<uint32_t>((reinterpret_cast<uintptr_t>(base) >> 1) & 1u);
+      base -= st.par;
+      bytes = ((a.Ci - 1 - st.c0) * cstride + a.hw) * 2;
+      bytes = bytes > 0 ? (bytes + 2 * st.par + 3) & ~int64_t(3) : 0;
+      bytes = bytes > 0x80000000ll ? 0x80000000ll : bytes;  // OOB stays out of range
+    }
     st.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0,
                                               static_cast<int>(bytes), 0x00020000);
     st.cs = static_cast<uint32_t>(cstride * 2);
@@ -221,6 +231,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
   uint32_t t_g8[TPT], t_pix[TPT], t_lds[TPT];
   bool t_st[TPT], t_ok[TPT], t_in[TPT];
   int t_w[TPT];
+  uint32_t t_mask[ALIGNED ? 1 : TPT][4];  // unaligned form: the pixels inside the frame
 #pragma unroll
   for (int tt = 0; tt < TPT; ++tt) {
     const int t = tid + tt * NT;
@@ -233,6 +244,10 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
     t_pix[tt] = static_cast<uint32_t>(gh * a.W + w) * 2u;
     t_lds[tt] = static_cast<uint32_t>((rr * TW + 1 + 8 * q) * PIXB + 16 * g);
     t_w[tt] = w;
+    if (!ALIGNED)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        t_mask[tt][e] = (w + 2 * e < a.W ? 0xffffu : 0u) | (w + 2 * e + 1 < a.W ? 0xffff0000u : 0u);
     // interior rows of the tile (the cache write covers only those)
     t_in[tt] = t_st[tt] & (rr >= 1) & (rr <= BH) & (gh < a.H) & (w < a.W);
   }
@@ -251,6 +266,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
   }
 
   u32x4 sv[TPT][8];
+  uint32_t sx[ALIGNED ? 1 : TPT][8];  // unaligned form: the dword after each segment's four
   uint16_t hv[HPT];
   // PRO: this thread's 8 task channels (8g + j, the same g for every task
   // of a thread) and its halo channels, for the stage being loaded; batch
@@ -293,16 +309,10 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
           sv[tt][j] = __builtin_bit_cast(
               u32x4, __builtin_amdgcn_raw_buffer_load_b128(st.rs, off + j * st.cs, 0, 0));
         } else {
-          uint32_t wd[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t o0 = (t_w[tt] + 2 * e < a.W) ? off + j * st.cs + 4u * e : OOB;
-            const uint32_t o1 = (t_w[tt] + 2 * e + 1 < a.W) ? off + j * st.cs + 4u * e + 2u : OOB;
-            const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(st.rs, o0, 0, 0);
-            const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(st.rs, o1, 0, 0);
-            wd[e] = (lo & 0xffffu) | (hi << 16);
-          }
-          sv[tt][j] = u32x4{wd[0], wd[1], wd[2], wd[3]};
+          // 20 dword-aligned bytes that hold the segment's 16 (fix_part)
+          const uint32_t at = t_ok[tt] ? (off + j * st.cs + 2u * st.par) & ~3u : OOB;
+          sv[tt][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(st.rs, at, 0, 0));
+          sx[tt][j] = __builtin_amdgcn_raw_buffer_load_b32(st.rs, at, 16, 0);
         }
       }
     }
@@ -310,7 +320,30 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
 #pragma unroll
     for (int hh = 0; hh < HPT; ++hh)
       hv[hh] = __builtin_amdgcn_raw_buffer_load_b16(
-          st.rs, h_ok[hh] ? h_ch[hh] * st.cs + h_pix[hh] : OOB, 0, 0);
+          st.rs, h_ok[hh] ? h_ch[hh] * st.cs + h_pix[hh] + 2u * st.par : OOB, 0, 0);
+  };
+
+  // Unaligned form: part `part` of a stage's segments shifted into place (by
+  // one element when the segment starts at an odd one), pixels past the
+  // frame's width set to zero.  An odd width used to be loaded element by
+  // element, eight loads a segment (and stored so): 256 -> 256 at 135x241, two
+  // frames, took 0.408 ms on the tiles that now take 0.275.
+  auto fix_part = [&](const Stage& st, int part) {
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int tt = 0; tt < TPT; ++tt) {
+        const uint32_t off = t_g8[tt] * st.cs + t_pix[tt] + 2u * st.par;
+#pragma unroll
+        for (int j = 2 * part; j < 2 * part + 2; ++j) {
+          const uint32_t sh = ((off + j * st.cs) & 2u) << 3;
+          const u32x4 v = sv[tt][j];
+          sv[tt][j] = u32x4{__builtin_amdgcn_alignbit(v[1], v[0], sh) & t_mask[tt][0],
+                            __builtin_amdgcn_alignbit(v[2], v[1], sh) & t_mask[tt][1],
+                            __builtin_amdgcn_alignbit(v[3], v[2], sh) & t_mask[tt][2],
+                            __builtin_amdgcn_alignbit(sx[tt][j], v[3], sh) & t_mask[tt][3]};
+        }
+      }
+    }
   };
 
   // PRO: the prologue on the staged registers of part `part` of a stage
@@ -392,6 +425,10 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
       for (int j = 0; j < 8; ++j) {
         if (ALIGNED) {
           __builtin_amdgcn_raw_buffer_store_b128(sv[tt][j], crs, off + j * ccs, 0, 0);
+        } else if (t_w[tt] + 8 <= a.W) {
+          // one store at any 2-byte alignment
+          if (t_in[tt] && st.c0 + static_cast<int>(t_g8[tt]) + j < a.Ci)
+            __builtin_memcpy(reinterpret_cast<unsigned char*>(cbase) + off + j * ccs, &sv[tt][j], 16);
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
@@ -475,6 +512,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
     load_w(cst.wbase, 0, wr[0]);
     load_w(cst.wbase, 1, wr[1]);
     for (int part = 0; part < 5; ++part) load_stage(cst, part);
+    for (int part = 0; part < 4; ++part) fix_part(cst, part);
     for (int part = 0; part < 5; ++part) pro_part(part);
     if (cache_needed(cst, true)) cache_store(cst);
     store_stage(0);
@@ -505,6 +543,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
       // PRO: the next stage's prologue, part p at step p + 3 (its loads were
       // issued at step p), the halo at step 6; all before the cache and LDS
       // stores of step 7
+      if (!ALIGNED && ij >= 3 && ij <= 6) fix_part(nst_, ij - 3);
       if (PRO && ij >= 3 && ij <= 6) pro_part(ij - 3);
       if (PRO && ij == 6) pro_part(4);
       if (ij == 7 && cache_needed(nst_, s + 1 < cnt)) cache_store(nst_);
@@ -533,7 +572,7 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
       // explicit interleave (masks: 0x008 MFMA, 0x100 DS read, 0x020 VMEM
       // read, 0x200 DS write): after each fragment's products, its re-read;
       // global reads spread over the first groups, LDS writes over all
-      constexpr int nvm_stage = 2 * TPT;
+      constexpr int nvm_stage = (ALIGNED ? 2 : 4) * TPT;
       const int nvm = WCO + (ij < 4 ? nvm_stage : ij == 4 ? HPT : 0);
       const int ndw = ij == 7 ? TPT * 8 + HPT : 0;
       const bool rd = ij + 1 < 9 || NBUF == 3;
@@ -573,8 +612,8 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
         const int h = h0 + wpx * WR + pf / WCF, w = w0 + (pf % WCF) * 16 + 4 * (lane >> 4);
         if (co >= a.Co || h >= a.H || w >= a.W) continue;
         float* dst = pbase + co * plane + static_cast<int64_t>(h) * a.W + w;
-        if (ALIGNED && w + 4 <= a.W) {
-          *reinterpret_cast<f32x4*>(dst) = acc[cf][pf];
+        if (w + 4 <= a.W) {
+          __builtin_memcpy(dst, &acc[cf][pf], 16);  // at any 4-byte alignment
         } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
@@ -604,6 +643,8 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
         const uint16_t* rsrc = has_r ? a.residual + off : a.y;
         if (ALIGNED) {
           rv[cf][pf] = *reinterpret_cast<const uint2*>(rsrc);
+        } else if (ok & (w + 4 <= a.W)) {
+          __builtin_memcpy(&rv[cf][pf], rsrc, 8);  // at any 2-byte alignment
         } else {
           uint16_t e[4];
 #pragma unroll
@@ -636,6 +677,9 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
           uint32_t, __builtin_convertvector((f32x2{acc[cf][pf][2] + bb + rr[2], acc[cf][pf][3] + bb + rr[3]}), bf16x2));
       if (ALIGNED && w + 4 <= a.W) {
         *reinterpret_cast<uint2*>(dst) = make_uint2(v01, v23);
+      } else if (w + 4 <= a.W) {
+        const uint2 v = make_uint2(v01, v23);
+        __builtin_memcpy(dst, &v, 8);  // at any 2-byte alignment
       } else {
         const uint16_t v[4] = {static_cast<uint16_t>(v01), static_cast<uint16_t>(v01 >> 16),
                                static_cast<uint16_t>(v23), static_cast<uint16_t>(v23 >> 16)};
@@ -686,7 +730,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
 }
 
 // Tile configurations of the bf16 kernel (template arguments of run()).
-enum Cfg { CFG_C192, CFG_C96, CFG_C16, CFG_C160_4X80, CFG_C160_10X32, CFG_C128_4X80, CFG_C64_4X64 };
+enum Cfg { CFG_C192, CFG_C96, CFG_C16, CFG_C160_4X80, CFG_C160_10X32, CFG_C128_4X80, CFG_C128_10X32, CFG_C64_4X64 };
 
 // Launch plan of one bf16 fast call: tile configuration, workgroups of one
 // split, split-K factor, and the fp32 partial-sum bytes the split needs.
@@ -842,6 +886,18 @@ Plan plan_bf16(const Geo& g) {
       p = r;
       p.cfg = CFG_C128_4X80;
     }
+    // the same on 10 x 32 pixels, for frames whose width 80-pixel tiles cover
+    // badly (256 -> 256 at 135x241, two frames: 448 workgroups of 128
+    // channels in two rounds, 0.217 ms, against 448 of 160 on 10 x 32, 0.275,
+    // or 544 of 128 on 4 x 80 in three)
+    Plan r2;
+    set_tiles(g, 128, 10, 32, &r2);
+    const int64_t pco = p.cfg == CFG_C128_4X80 ? 128 : 160;
+    if (r2.tiles_co * 128 <= p.tiles_co * pco &&
+        ((r2.blocks + cus - 1) / cus) * 128 < ((p.blocks + cus - 1) / cus) * pco) {
+      p = r2;
+      p.cfg = CFG_C128_10X32;
+    }
   }
   p.splits = 1;
   p.part_bytes = 0;
@@ -895,7 +951,7 @@ Plan unsplit_plan(const Geo& g, Plan p) {
   p.splits = 1;
   p.part_bytes = 0;
   const bool wide = p.cfg == CFG_C192 || p.cfg == CFG_C160_4X80 || p.cfg == CFG_C160_10X32 ||
-                    p.cfg == CFG_C128_4X80;
+                    p.cfg == CFG_C128_4X80 || p.cfg == CFG_C128_10X32;
   if (g.channel_tiles || !wide || p.blocks >= cus) return p;
   // cost in tenths of c
   auto cost = [&](const Plan& q, int64_t c10) {
@@ -990,6 +1046,7 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
     // layers for this tile (the 192- and 96-channel tiles keep three)
     case CFG_C160_4X80: return run<5, 2, 5, 2, 2, 2>(g, a, pl, aligned, fused, s, info);
     case CFG_C128_4X80: return run<4, 2, 5, 2, 2, 2>(g, a, pl, aligned, fused, s, info);
+    case CFG_C128_10X32: return run<4, 5, 2, 2, 2, 3>(g, a, pl, aligned, fused, s, info);
     // two fragments per wave: 64 x 4x64 tiles for unsplit calls that fill few compute units
     case CFG_C64_4X64: return run<2, 2, 4, 2, 2, 3>(g, a, pl, aligned, fused, s, info);
     default: return run<5, 5, 2, 2, 2, 3>(g, a, pl, aligned, fused, s, info);

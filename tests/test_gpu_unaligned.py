@@ -1,0 +1,112 @@
+"""The bf16 kernels on tensors and frames that 16-byte accesses do not fit:
+odd widths (against the oracle) and tensors at odd element addresses, whose
+results must be the aligned call's bit for bit: the tile and the order of
+every sum are the same, only the loads and stores differ.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_31938_amd import c3c, inputs
+from paper_2609_31938_amd.inputs import spec
+
+from gpu_util import as_f64, check, chunk, guarded, guards_intact, host, layer, oracle_args, say
+
+pytestmark = pytest.mark.gpu
+
+PIN = c3c.MODE_CHANNEL_TILES
+# (mode, tile, shape): every tile of the 3x3 kernel
+TILES = [
+    (PIN, (16, 8, 64), dict(Co=12, H=11, W=72)),
+    (0, (96, 6, 64), dict(Co=90, H=9, W=72)),
+    (PIN, (128, 4, 80), dict(Co=256, H=9, W=88)),
+    (PIN, (128, 10, 32), dict(Co=256, T=4, H=153, W=40)),
+    (PIN, (160, 4, 80), dict(Co=150, H=9, W=88)),
+    (PIN, (160, 10, 32), dict(Co=150, T=4, H=333, W=32)),
+    (PIN, (192, 4, 64), dict(Co=192, H=9, W=72)),
+    (0, (64, 4, 64), dict(Co=192, H=9, W=72)),
+]
+
+
+def _at(t, offset):
+    """The same values ``offset`` elements past a 16-byte address."""
+    buf = torch.full((t.numel() + 16,), float("nan"), dtype=t.dtype, device=t.device)
+    v = buf[offset:offset + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+def _call(sp, mode, offset, form, ws):
+    ctx = c3c.Context(mode)
+    w, b = layer(sp, "bf16", 917)
+    x, cache = chunk(sp, "bf16", 917, 0, 0), chunk(dict(sp, T=sp["Tc"]), "bf16", 917, 0, 1)
+    To, Ho, Wo, L = c3c.output_dims(sp, "bf16")
+    y = torch.full((sp["N"], sp["Co"], To, Ho, Wo), float("nan"), dtype=torch.bfloat16, device="cuda")
+    co = torch.full((sp["N"], sp["Ci"], L, Ho, Wo), float("nan"), dtype=torch.bfloat16, device="cuda")
+    need = c3c.workspace_bytes(sp, "bf16") if ws else 0
+    if ws:
+        assert need > 0
+        ctx.set_workspace(torch.empty(need, dtype=torch.uint8, device="cuda"))
+    x, cache, y, co = (_at(t, offset) for t in (x, cache, y, co))
+    args = (ctx, sp, x, cache, w, c3c.weight_repack(ctx, sp, w), b)
+    if form == "plain":
+        c3c.conv3d_causal_cached(*args, y, co)
+    else:
+        res = _at(inputs.residual_input(tuple(y.shape), "bf16", 917, 0, 0, "cuda"), offset)
+        sc, sh = inputs.affine_inputs(sp, 917, 0, 0, "cuda") if form == "prologue" else (None, None)
+        c3c.conv3d_causal_cached_fused(*args, sc, sh, res, y, co)
+    torch.cuda.synchronize()
+    return y, co
+
+
+@pytest.mark.parametrize("form", ["plain", "residual", "prologue"])
+@pytest.mark.parametrize("mode,tile,over", TILES)
+def test_odd_addresses_give_the_aligned_result(mode, tile, over, form):
+    sp = spec(**dict(dict(Ci=40, T=2, Tc=2), **over))
+    plan = c3c.plan_query(c3c.Context(mode), sp, "bf16")
+    say(f"unaligned case {sp} {form} plan={plan}")
+    assert (plan["tile_co"], plan["tile_h"], plan["tile_w"]) == tile, plan
+    want = _call(sp, mode, 0, form, False)
+    for offset in (1, 2):
+        got = _call(sp, mode, offset, form, False)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), offset
+
+
+@pytest.mark.parametrize("form", ["plain", "residual"])
+def test_odd_addresses_under_split_k(form):
+    sp = spec(Ci=256, Co=192, T=1, Tc=2, H=9, W=72)
+    say(f"unaligned split-K case {sp} {form}")
+    want = _call(sp, 0, 0, form, True)
+    for offset in (1, 2):
+        got = _call(sp, 0, offset, form, True)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), offset
+
+
+@pytest.mark.parametrize("over", [
+    dict(Ci=40, Co=192, H=9, W=67), dict(Ci=33, Co=256, T=4, H=153, W=37), dict(Ci=31, Co=96, H=13, W=65),
+    dict(Ci=40, Co=150, H=5, W=81), dict(N=2, Ci=35, Co=20, H=7, W=3), dict(Ci=256, Co=192, T=1, H=9, W=71),
+    dict(Ci=40, Co=60, H=1, W=1),
+])
+@pytest.mark.parametrize("ws", [False, True])
+def test_odd_widths_match_the_oracle(over, ws):
+    sp = spec(**dict(dict(T=2, Tc=2), **over))
+    ctx = c3c.Context(c3c.MODE_STRICT)
+    need = c3c.workspace_bytes(sp, "bf16") if ws else 0
+    if ws and need == 0:
+        pytest.skip("runs unsplit")
+    say(f"odd width case {sp} ws={ws} plan={c3c.plan_query(ctx, sp, 'bf16', need)}")
+    if need:
+        ctx.set_workspace(torch.empty(need, dtype=torch.uint8, device="cuda"))
+    w, b = layer(sp, "bf16", 917)
+    x, cache = chunk(sp, "bf16", 917, 0, 0), chunk(dict(sp, T=2), "bf16", 917, 0, 1)
+    To, Ho, Wo, L = c3c.output_dims(sp, "bf16")
+    y, ybuf = guarded((sp["N"], sp["Co"], To, Ho, Wo), "bf16")
+    co, cbuf = guarded((sp["N"], sp["Ci"], L, Ho, Wo), "bf16")
+    c3c.conv3d_causal_cached(ctx, sp, x, cache, w, c3c.weight_repack(ctx, sp, w), b, y, co)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf) and guards_intact(cbuf), "a write outside the outputs"
+    args = oracle_args(sp, x, cache, w, b)
+    check(as_f64(y), oracle.conv3d(sp, "bf16", *args), "bf16", str(sp))
+    got = host(co).contiguous().view(torch.int16).numpy().view(np.uint16)
+    assert np.array_equal(got, oracle.cache_update(sp, "bf16", args[0], args[1]))
