@@ -310,7 +310,10 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
               u32x4, __builtin_amdgcn_raw_buffer_load_b128(st.rs, off + j * st.cs, 0, 0));
         } else {
           // 20 dword-aligned bytes that hold the segment's 16 (fix_part)
-          const uint32_t at = t_ok[tt] ? (off + j * st.cs + 2u * st.par) & ~3u : OOB;
+          // (a channel past Ci is kept out by hand: the rounded-up size may
+          // hold one element after the source)
+          const bool real = t_ok[tt] & (st.c0 + static_cast<int>(t_g8[tt]) + j < a.Ci);
+          const uint32_t at = real ? (off + j * st.cs + 2u * st.par) & ~3u : OOB;
           sv[tt][j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(st.rs, at, 0, 0));
           sx[tt][j] = __builtin_amdgcn_raw_buffer_load_b32(st.rs, at, 16, 0);
         }

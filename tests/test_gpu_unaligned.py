@@ -26,6 +26,9 @@ TILES = [
     (PIN, (160, 10, 32), dict(Co=150, T=4, H=333, W=32)),
     (PIN, (192, 4, 64), dict(Co=192, H=9, W=72)),
     (0, (64, 4, 64), dict(Co=192, H=9, W=72)),
+    # one frame a source: the element after the last real channel is the
+    # first of the padding channels (NaN here), and must not be read as one
+    (0, (96, 6, 64), dict(Co=90, T=1, Tc=1, H=9, W=72)),
 ]
 
 
