@@ -39,7 +39,10 @@
 // otherwise the caller copies it).
 // Calls with one output frame take the chunk-stage form further down.
 //
-// Requires H * W a multiple of 8 and 16-byte-aligned x / cache, 8-byte y.
+// Aligned calls have H * W a multiple of 8 and 16-byte-aligned x / cache,
+// 8-byte y (AL); any other call takes the instance without AL, whose row
+// segments load as 20 dword-aligned bytes, shifted into place on their way to
+// LDS, and whose outputs and cache rows store at any 2-byte alignment.
 #include "c3c_internal.h"
 
 #include <type_traits>
@@ -89,6 +92,16 @@ struct TapArgs {
   int L, write_cache;
 };
 
+// One stage's activations of a thread in registers.  Without AL a segment's
+// eight pixels lie in 20 dword-aligned bytes, v and x, the first of them one
+// element in when sh is 16.
+template <bool AL>
+struct ActRegs {
+  u32x4 v[TSPT];
+  uint32_t x[AL ? 1 : TSPT], sh[AL ? 1 : TSPT];
+};
+
+template <bool AL>
 __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
   __shared__ __align__(16) unsigned char lds[2 * TBUF];
   constexpr uint32_t OOB = 0x80000000u;  // beyond every resource's size
@@ -160,13 +173,17 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
     astep = TK * cstride;
   };
   act_tap();
-  auto next_rsrc = [&](uint32_t& cs) __attribute__((always_inline)) {
+  auto next_rsrc = [&](uint32_t& cs, uint32_t& par, uint32_t& rows) __attribute__((always_inline)) {
     const bool real = ak <= k_hi;
-    const uint32_t bytes = real ? static_cast<uint32_t>(min(TK, a.Ci - ac * TK) - 1) * acs +
-                                      static_cast<uint32_t>(a.hw - px0) * 2u
-                                : 0u;
+    rows = static_cast<uint32_t>(min(TK, a.Ci - ac * TK));
+    uint32_t bytes = real ? (rows - 1) * acs + static_cast<uint32_t>(a.hw - px0) * 2u : 0u;
+    // without AL: dword-aligned base and size (the dword of the last element
+    // included), par elements before the source; that dword may hold one
+    // element after the source, so rows past the last are kept out by hand
+    par = AL ? 0u : static_cast<uint32_t>((reinterpret_cast<uintptr_t>(ap) >> 1) & 1u);
+    if (!AL) bytes = real ? (bytes + 2u * par + 3u) & ~3u : 0u;
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(ap), 0, static_cast<int>(bytes), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(ap - par), 0, static_cast<int>(bytes), 0x00020000);
     cs = acs;
     if (++ac == a.chunks) {
       ac = 0;
@@ -188,12 +205,19 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
     s_px[i] = static_cast<uint32_t>(c) * 16u;
     s_lds[i] = static_cast<uint32_t>(row_off(r) + c * 16);
   }
-  auto load_act = [&](u32x4 (&v)[TSPT]) {
-    uint32_t cs;
-    const __amdgpu_buffer_rsrc_t rs = next_rsrc(cs);
+  auto load_act = [&](ActRegs<AL>& r) {
+    uint32_t cs, par, rows;
+    const __amdgpu_buffer_rsrc_t rs = next_rsrc(cs, par, rows);
 #pragma unroll
-    for (int i = 0; i < TSPT; ++i)
-      v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, s_row[i] * cs + s_px[i], 0, 0));
+    for (int i = 0; i < TSPT; ++i) {
+      const uint32_t off = s_row[i] * cs + s_px[i] + 2u * par;
+      const uint32_t at = AL ? off : s_row[i] < rows ? off & ~3u : OOB;
+      r.v[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0));
+      if constexpr (!AL) {
+        r.x[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, 16, 0);
+        r.sh[i] = (off & 2u) << 3;
+      }
+    }
   };
   // the next stage's activations (stages are stored in order: tap sk,
   // chunk sc) into LDS buffer buf; a stage whose frame goes to the new cache
@@ -201,7 +225,17 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
   // from the same registers (the chunk's real rows, pixels inside the plane)
   const int64_t cl = static_cast<int64_t>(a.L) * a.hw;
   int sk = k_lo, sc = 0;
-  auto store_act = [&](const u32x4 (&v)[TSPT], int buf) __attribute__((always_inline)) {
+  auto store_act = [&](const ActRegs<AL>& r, int buf) __attribute__((always_inline)) {
+    u32x4 v[TSPT];
+#pragma unroll
+    for (int i = 0; i < TSPT; ++i) {
+      v[i] = r.v[i];
+      if constexpr (!AL)
+        v[i] = u32x4{__builtin_amdgcn_alignbit(r.v[i][1], r.v[i][0], r.sh[i]),
+                     __builtin_amdgcn_alignbit(r.v[i][2], r.v[i][1], r.sh[i]),
+                     __builtin_amdgcn_alignbit(r.v[i][3], r.v[i][2], r.sh[i]),
+                     __builtin_amdgcn_alignbit(r.x[i], r.v[i][3], r.sh[i])};
+    }
 #pragma unroll
     for (int i = 0; i < TSPT; ++i) *reinterpret_cast<u32x4*>(lds + buf * TBUF + s_lds[i]) = v[i];
     const int k = sk, c0 = sc * TK;
@@ -213,14 +247,26 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
       const int f = t * a.st + k * a.dt - a.p_l;
       const uint32_t ccs = static_cast<uint32_t>(cl * 2);
       const uint32_t cbytes = static_cast<uint32_t>(min(TK, a.Ci - c0) - 1) * ccs + static_cast<uint32_t>(a.hw) * 2u;
-      const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
-          a.cache_out + (static_cast<int64_t>(n) * a.Ci + c0) * cl + static_cast<int64_t>(f - (a.Z - a.L)) * a.hw,
-          0, static_cast<int>(cbytes), 0x00020000);
+      uint16_t* cbase =
+          a.cache_out + (static_cast<int64_t>(n) * a.Ci + c0) * cl + static_cast<int64_t>(f - (a.Z - a.L)) * a.hw;
+      const __amdgpu_buffer_rsrc_t crs =
+          __builtin_amdgcn_make_buffer_rsrc(cbase, 0, static_cast<int>(cbytes), 0x00020000);
 #pragma unroll
       for (int i = 0; i < TSPT; ++i) {
         const uint32_t px = px0 + s_px[i] / 2u;
-        __builtin_amdgcn_raw_buffer_store_b128(v[i], crs,
-                                               px < static_cast<uint32_t>(a.hw) ? s_row[i] * ccs + px * 2u : OOB, 0, 0);
+        if constexpr (AL) {
+          __builtin_amdgcn_raw_buffer_store_b128(v[i], crs,
+                                                 px < static_cast<uint32_t>(a.hw) ? s_row[i] * ccs + px * 2u : OOB, 0, 0);
+        } else if (c0 + static_cast<int>(s_row[i]) < a.Ci) {
+          uint16_t* dst = cbase + static_cast<int64_t>(s_row[i]) * cl + px;
+          if (px + 8 <= static_cast<uint32_t>(a.hw)) {
+            __builtin_memcpy(dst, &v[i], 16);  // at any 2-byte alignment
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (px + e < static_cast<uint32_t>(a.hw)) dst[e] = static_cast<uint16_t>(v[i][e >> 1] >> (16 * (e & 1)));
+          }
+        }
       }
     }
   };
@@ -285,7 +331,7 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
 
   // prologue: weights of stage 0, activations of stages 0 and 1 in flight,
   // stage 0 into LDS buffer 0
-  u32x4 act0[TSPT], act1[TSPT];
+  ActRegs<AL> act0, act1;
   u32x4 w0[WCO], w1[WCO];
   load_w(w0);
   load_act(act0);
@@ -297,8 +343,8 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
   // register sets were consumed in stage s - 1), the products of s, then
   // s + 1's activations into the other buffer (last read in stage s - 1,
   // before its barrier)
-  auto stage = [&](int buf, const u32x4 (&w_cur)[WCO], u32x4 (&w_nxt)[WCO], u32x4 (&a_free)[TSPT],
-                   const u32x4 (&a_next)[TSPT]) {
+  auto stage = [&](int buf, const u32x4 (&w_cur)[WCO], u32x4 (&w_nxt)[WCO], ActRegs<AL>& a_free,
+                   const ActRegs<AL>& a_next) {
     load_w(w_nxt);
     load_act(a_free);
     i16x8 av[NPF];
@@ -335,8 +381,17 @@ __global__ __launch_bounds__(256, 2) void conv_tap1x1(TapArgs a) {
           uint32_t, __builtin_convertvector((f32x2{acc[cf][pf][0] + bb, acc[cf][pf][1] + bb}), bf16x2));
       const uint32_t v23 = __builtin_bit_cast(
           uint32_t, __builtin_convertvector((f32x2{acc[cf][pf][2] + bb, acc[cf][pf][3] + bb}), bf16x2));
-      // H * W is a multiple of 8, so 4 pixels from a multiple of 4 stay in the plane
-      *reinterpret_cast<uint2*>(yrow + p) = make_uint2(v01, v23);
+      const uint2 v = make_uint2(v01, v23);
+      if constexpr (AL) {
+        // H * W is a multiple of 8, so 4 pixels from a multiple of 4 stay in the plane
+        *reinterpret_cast<uint2*>(yrow + p) = v;
+      } else if (p + 4 <= a.hw) {
+        __builtin_memcpy(yrow + p, &v, 8);  // at any 2-byte alignment
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          if (p + r < a.hw) yrow[p + r] = static_cast<uint16_t>((r < 2 ? v01 : v23) >> (16 * (r & 1)));
+      }
     }
   }
 }
@@ -647,15 +702,12 @@ bool aligned_to(const void* p, uintptr_t m) { return (reinterpret_cast<uintptr_t
 
 }  // namespace
 
-bool tap1x1_eligible(const Geo& g, const void* x, const void* cache, const void* y) {
+bool tap1x1_eligible(const Geo& g) {
   const c3c_conv_desc& d = g.d;
   // buffer offsets are 32-bit: one 32-channel stage slab and the packed weights must fit
   const int64_t frames = d.T > d.Tc ? d.T : d.Tc;
-  if (static_cast<int64_t>(TK) * frames * d.H * d.W * 2 >= 0x7fffffff ||
-      pack_dims(d).elems() * 2 >= 0x7fffffff)
-    return false;
-  return (d.H * d.W) % 8 == 0 && aligned_to(x, 16) && (cache == nullptr || aligned_to(cache, 16)) &&
-         aligned_to(y, 8);
+  return static_cast<int64_t>(TK) * frames * d.H * d.W * 2 < 0x7fffffff &&
+         pack_dims(d).elems() * 2 < 0x7fffffff;
 }
 
 int64_t tap1x1_blocks(const Geo& g) {
@@ -688,7 +740,9 @@ hipError_t launch_tap1x1(const Geo& g, const void* x, const void* cache, const v
   const c3c_conv_desc& d = g.d;
   const PackDims p = pack_dims(d);
   if (cache_written) *cache_written = false;
-  if (!tap1x1_eligible(g, x, cache, y)) return hipErrorInvalidValue;
+  if (!tap1x1_eligible(g)) return hipErrorInvalidValue;
+  const bool al = (d.H * d.W) % 8 == 0 && aligned_to(x, 16) && (cache == nullptr || aligned_to(cache, 16)) &&
+                  aligned_to(y, 8);
   TapArgs a;
   a.x = static_cast<const uint16_t*>(x);
   a.cache = static_cast<const uint16_t*>(cache);
@@ -716,16 +770,16 @@ hipError_t launch_tap1x1(const Geo& g, const void* x, const void* cache, const v
   a.cache_out = static_cast<uint16_t*>(cache_out);
   a.L = static_cast<int>(g.L);
   a.write_cache = 0;
-  // the chunk-stage form for one output frame (Kt <= 3), else one stage per
-  // tap and chunk
+  // the chunk-stage form for one output frame of an aligned call (Kt <= 3),
+  // else one stage per tap and chunk
   // (its source offsets span every channel of a frame, three chunks past the
   // last included, and its new-cache offsets every channel and frame, in 32
   // bits)
-  const bool chunk_form = g.To == 1 && d.Kt <= KTG &&
+  const bool chunk_form = al && g.To == 1 && d.Kt <= KTG &&
                           (d.Ci + 3 * TK) * (d.T + d.Tc) * d.H * d.W * 2 < 0x7fffffff;
   // the new cache from the staged tiles when every frame of it is staged
   // (32-bit offsets within a 32-channel slab of it; a tap mask of 32 bits)
-  a.write_cache = g.L > 0 && cache_out != nullptr && aligned_to(cache_out, 16) && d.Kt <= 32 &&
+  a.write_cache = g.L > 0 && cache_out != nullptr && (!al || aligned_to(cache_out, 16)) && d.Kt <= 32 &&
                   static_cast<int64_t>(TK) * g.L * a.hw * 2 < 0x7fffffff && stages_new_cache(g);
   const int64_t blocks = tap1x1_blocks(g);
   if (info) {
@@ -745,8 +799,10 @@ hipError_t launch_tap1x1(const Geo& g, const void* x, const void* cache, const v
   const dim3 grid(static_cast<unsigned>(blocks)), block(256);
   if (chunk_form)
     hipLaunchKernelGGL(conv_tap1x1_chunk, grid, block, 0, s, a);
+  else if (al)
+    hipLaunchKernelGGL(conv_tap1x1<true>, grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL(conv_tap1x1, grid, block, 0, s, a);
+    hipLaunchKernelGGL(conv_tap1x1<false>, grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -111,7 +111,8 @@ __device__ inline f32x4 mma(i16x8 a, u32x4 b, f32x4 c) {
 // PACKED: weights in matrix-core fragment order (fast route, bf16); else
 // w[co][ci] (fallback, Kt = 1).  ALIGNED: every channel plane starts on a
 // 16-byte boundary (H * W a multiple of 8, aligned pointers); else the
-// activations are read 2 bytes at a time and the outputs stored one by one.
+// row segments load as 20 dword-aligned bytes, shifted into place on their way
+// to LDS, and the outputs store at any 2-byte alignment.
 // FU (bf16): the fused form.  1: the residual, in the epilogue.  2: also
 // the prologue on stages whose frame comes from the new chunk (applied to
 // the staged registers before they go to LDS; a 1x1 kernel has no spatial
@@ -209,6 +210,7 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
   }
   struct Chunk {
     u32x4 x[SEG];
+    uint32_t xx[ALIGNED ? 1 : SEG], sh;  // !ALIGNED: the dword after each segment's four; their shift (0 or 16)
     u32x4 w[PW_WPT];
     float psc, psh;  // PRO: this thread's channel's scale and shift
     bool pro;        // PRO: the stage's frame comes from the new chunk
@@ -222,11 +224,15 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
       PRO && a.shift ? a.Ci * 4 : 0, 0x00020000);
   auto load_chunk = [&](Chunk& ck) __attribute__((always_inline)) {
     const bool real = lk <= k_hi;
-    const uint32_t bytes = real ? static_cast<uint32_t>(min(PW_K, a.Ci - lc * PW_K) - 1) * lcs +
-                                      static_cast<uint32_t>(a.hw - px0) * 2u
-                                : 0u;
+    const uint32_t rows = static_cast<uint32_t>(min(PW_K, a.Ci - lc * PW_K));
+    uint32_t bytes = real ? (rows - 1) * lcs + static_cast<uint32_t>(a.hw - px0) * 2u : 0u;
+    // !ALIGNED: dword-aligned base and size (the dword of the last element
+    // included), par elements before the source; that dword may hold one
+    // element after the source, so rows past the last are kept out by hand
+    const uint32_t par = ALIGNED ? 0u : static_cast<uint32_t>((reinterpret_cast<uintptr_t>(lp) >> 1) & 1u);
+    if (!ALIGNED) bytes = real ? (bytes + 2u * par + 3u) & ~3u : 0u;
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(lp), 0, static_cast<int>(bytes), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(lp - par), 0, static_cast<int>(bytes), 0x00020000);
     if constexpr (PRO) {
       // the prologue applies to the new chunk's frames only
       const bool from_x = real && lfx;
@@ -241,17 +247,13 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
       for (int h = 0; h < SEG; ++h)
         ck.x[h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, soff + 256u * h, 0, 0));
     } else {
+      const uint32_t off = soff + 2u * par;
+      ck.sh = (off & 2u) << 3;
 #pragma unroll
       for (int h = 0; h < SEG; ++h) {
-        uint32_t wd[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t o = soff + 256u * h + 4u * e;
-          const uint32_t lo = __builtin_amdgcn_raw_buffer_load_b16(rs, o, 0, 0);
-          const uint32_t hi = __builtin_amdgcn_raw_buffer_load_b16(rs, o + 2u, 0, 0);
-          wd[e] = (lo & 0xffffu) | (hi << 16);
-        }
-        ck.x[h] = u32x4{wd[0], wd[1], wd[2], wd[3]};
+        const uint32_t at = static_cast<uint32_t>(sch) < rows ? (off & ~3u) + 256u * h : OOB;
+        ck.x[h] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0));
+        ck.xx[h] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, 16, 0);
       }
     }
     if constexpr (PACKED) {
@@ -285,6 +287,9 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
     for (int h = 0; h < SEG; ++h) {
       // PRO: the prologue on a new-chunk stage (a workgroup-uniform test)
       u32x4 v = ck.x[h];
+      if constexpr (!ALIGNED)
+        v = u32x4{__builtin_amdgcn_alignbit(v[1], v[0], ck.sh), __builtin_amdgcn_alignbit(v[2], v[1], ck.sh),
+                  __builtin_amdgcn_alignbit(v[3], v[2], ck.sh), __builtin_amdgcn_alignbit(ck.xx[h], v[3], ck.sh)};
       if (PRO && ck.pro) v = fuse_seg8(v, ck.psc, ck.psh, true);
       *reinterpret_cast<u32x4*>(base + slds + 256 * h) = v;
     }
@@ -386,6 +391,8 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
         const int p = px0 + wpx * 16 * PW_NPF + pf * 16 + 4 * g;
         if (ALIGNED) {
           rv[pf] = *reinterpret_cast<const uint2*>(rrow + (p + 4 <= a.hw ? p : 0));
+        } else if (p + 4 <= a.hw) {
+          __builtin_memcpy(&rv[pf], rrow + p, 8);  // at any 2-byte alignment
         } else {
           uint16_t e[4];
 #pragma unroll
@@ -413,6 +420,8 @@ __global__ __launch_bounds__(PW_NT, 1) void pointwise_conv(PwArgs a) {
       if (ALIGNED && p + 4 <= a.hw) {
         *reinterpret_cast<uint2*>(yrow + p) = make_uint2(v[0] | (static_cast<uint32_t>(v[1]) << 16),
                                                         v[2] | (static_cast<uint32_t>(v[3]) << 16));
+      } else if (p + 4 <= a.hw) {
+        __builtin_memcpy(yrow + p, v, 8);  // at any 2-byte alignment
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)

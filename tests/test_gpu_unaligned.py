@@ -12,6 +12,7 @@ from paper_2609_31938_amd import c3c, inputs
 from paper_2609_31938_amd.inputs import spec
 
 from gpu_util import as_f64, check, chunk, guarded, guards_intact, host, layer, oracle_args, say
+from test_gpu_fused import _check_cache
 
 pytestmark = pytest.mark.gpu
 
@@ -113,3 +114,57 @@ def test_odd_widths_match_the_oracle(over, ws):
     check(as_f64(y), oracle.conv3d(sp, "bf16", *args), "bf16", str(sp))
     got = host(co).contiguous().view(torch.int16).numpy().view(np.uint16)
     assert np.array_equal(got, oracle.cache_update(sp, "bf16", args[0], args[1]))
+
+
+# the temporal (1x1 spatial) kernels: 192 x 128-pixel tiles and the
+# 160 x 256 pointwise tiles, with ragged channels and pixel tiles, stride
+# 2, one source frame a tensor, new-cache frames in and out of the kernel
+TEMPORAL = [
+    ("tap1x1", dict(Ci=40, Co=192, T=4, Tc=2, H=63, W=67)),
+    ("tap1x1", dict(N=2, Ci=33, Co=180, T=8, Tc=1, H=59, W=37, s_t=2, p_base=1)),
+    ("tap1x1", dict(Ci=72, Co=384, T=1, Tc=1, H=95, W=91)),
+    ("tap1x1", dict(Ci=31, Co=768, T=3, Tc=0, H=43, W=31, p_base=2)),
+    ("pointwise", dict(Ci=40, Co=150, T=2, Tc=2, H=21, W=27)),
+    ("pointwise", dict(N=2, Ci=33, Co=330, T=1, Tc=1, H=17, W=19)),
+    ("pointwise", dict(Ci=100, Co=16, T=2, Tc=2, H=1, W=3)),
+]
+
+
+@pytest.mark.parametrize("form", ["plain", "residual", "prologue"])
+@pytest.mark.parametrize("kernel,over", TEMPORAL)
+def test_temporal_odd_planes_match_the_oracle(kernel, over, form):
+    sp = spec(Kh=1, Kw=1, **over)
+    ctx = c3c.Context(c3c.MODE_STRICT)
+    say(f"temporal odd plane case {sp} {form} plan={c3c.plan_query(ctx, sp, 'bf16')}")
+    w, b = layer(sp, "bf16", 917)
+    x = chunk(sp, "bf16", 917, 0, 0)
+    cache = chunk(dict(sp, T=sp["Tc"]), "bf16", 917, 0, 1) if sp["Tc"] else None
+    To, Ho, Wo, L = c3c.output_dims(sp, "bf16")
+    shape = (sp["N"], sp["Co"], To, Ho, Wo)
+    fused = {}
+    if form != "plain":
+        fused["residual"] = _at(inputs.residual_input(shape, "bf16", 917, 0, 0, "cuda"), 1)
+        if form == "prologue":
+            fused["scale"], fused["shift"] = inputs.affine_inputs(sp, 917, 0, 0, "cuda")
+    sc, sh, res = fused.get("scale"), fused.get("shift"), fused.get("residual")
+    # at odd addresses too, NaN on both sides
+    xo, co_ = _at(x, 1), _at(cache, 3) if cache is not None else None
+    y, ybuf = guarded(shape, "bf16")
+    co, cbuf = guarded((sp["N"], sp["Ci"], L, Ho, Wo), "bf16")
+    wp = c3c.weight_repack(ctx, sp, w)
+    if form == "plain":
+        assert c3c.plan_query(ctx, sp, "bf16")["kernel"] == kernel
+        c3c.conv3d_causal_cached(ctx, sp, xo, co_, w, wp, b, y, co)
+    else:
+        c3c.conv3d_causal_cached_fused(ctx, sp, xo, co_, w, wp, b, sc, sh, res, y, co)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf) and guards_intact(cbuf), "a write outside the outputs"
+    args = oracle_args(sp, x, cache, w, b)
+    if form == "plain":
+        ref, ref_c = oracle.conv3d(sp, "bf16", *args), oracle.cache_update(sp, "bf16", args[0], args[1])
+    else:
+        sch, shh = (t.cpu() if t is not None else None for t in (sc, sh))
+        ref, ref_c = oracle.conv3d_fused(sp, *args, sch, shh, res.cpu())
+    check(as_f64(y), ref, "bf16", str(sp))
+    got = host(co).contiguous().view(torch.int16).numpy().view(np.uint16)
+    _check_cache(got, ref_c, sp) if form == "prologue" else np.testing.assert_array_equal(got, ref_c)
