@@ -92,8 +92,9 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
 // fp32 partial-sum bytes a bf16 fast call would split into (0: it runs unsplit)
 int64_t fast_bf16_workspace_bytes(const Geo& g);
 // fallback, pointwise case (pointwise.hip): 1x1x1, unit spatial stride, no
-// spatial padding, one group, bf16 / fp16, aligned buffers
-bool pointwise_eligible(const Geo& g, const void* x, const void* cache, const void* w, const void* y);
+// spatial padding, one group, bf16 / fp16, 8-channel groups of aligned weights
+bool pointwise_eligible(const Geo& g, const void* x, const void* cache, const void* w, const void* y,
+                        const void* residual);
 hipError_t launch_pointwise(const Geo& g, const void* x, const void* cache, const void* w,
                             const void* bias, void* y, hipStream_t s, const Fuse& fu = Fuse{},
                             LaunchInfo* info = nullptr);

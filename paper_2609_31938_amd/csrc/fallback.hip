@@ -343,9 +343,7 @@ hipError_t launch_fallback(const Geo& g, const void* x, const void* cache, const
                            const void* bias, void* y, hipStream_t s, const Fuse& fu,
                            LaunchInfo* info) {
   if (g.To == 0) return hipSuccess;
-  // the pointwise kernel's aligned epilogue also reads the residual 8 bytes at a time
-  if (pointwise_eligible(g, x, cache, w, y) &&
-      (fu.residual == nullptr || (reinterpret_cast<uintptr_t>(fu.residual) & 7) == 0))
+  if (pointwise_eligible(g, x, cache, w, y, fu.residual))
     return launch_pointwise(g, x, cache, w, bias, y, s, fu, info);
   if (g.d.dtype == C3C_DTYPE_F32) return launch_fb<float>(g, x, cache, w, bias, y, s, fu, info);
   hipError_t e;
