@@ -9,12 +9,12 @@
 // channels.  Source frame of tap k for output frame o: o s_t + k d_t - p_l
 // (s_t is 1 for the 3x3 form).
 //
-// Workgroup: 32 output channels x 128 pixels of one output frame, a BH x BW
-// block whose shape the host picks for the frame (any BW: a pixel's place in
-// the staged tile is a per-lane address), or 128 consecutive pixels of the
-// plane for a 1x1 kernel.  4 x WK waves: wave (wpx, wk) owns 32 pixels and
-// every WK-th channel pair of a stage; the WK partial sums of a pixel are
-// added through LDS in a fixed order at the end.
+// Workgroup: 32 output channels x 32 PXW pixels (128, or 32 for small frames)
+// of one output frame, a BH x BW block whose shape the host picks for the
+// frame (any BW: a pixel's place in the staged tile is a per-lane address), or
+// consecutive pixels of the plane for a 1x1 kernel.  PXW x WK waves: wave
+// (wpx, wk) owns 32 pixels and every WK-th channel pair of a stage; the WK
+// partial sums of a pixel are added through LDS in a fixed order at the end.
 //
 // The product takes 64 cycles for 4096 FLOP, so one weight load (256 bytes)
 // and one LDS read a product are cheap, and NCHW planes are staged as they
@@ -40,7 +40,6 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int F_NPX = 128;  // pixels per workgroup
 constexpr int F_CO = 32;    // output channels per workgroup
 
 struct F32Args {
@@ -61,10 +60,12 @@ struct F32Args {
 };
 
 // KS: spatial kernel, 3 (pad 1) or 1 (the plane as one row).  CB: channels
-// per stage.  NR: 64-float pieces of a channel's staged tile.
-template <int KS, int CB, int NR, int WK>
-__global__ __launch_bounds__(256 * WK, WK == 1 ? 3 : 2) void fast_conv3d(F32Args a) {
-  constexpr int NW = 4 * WK, CPW = CB / NW;  // waves; channels a wave stages
+// per stage.  NR: 64-float pieces of a channel's staged tile.  PXW: waves
+// along the pixels.
+template <int KS, int CB, int NR, int PXW, int WK>
+__global__ __launch_bounds__(64 * PXW * WK, PXW * WK == 4 ? 3 : 2) void fast_conv3d(F32Args a) {
+  constexpr int F_NPX = 32 * PXW;            // pixels per workgroup
+  constexpr int NW = PXW * WK, CPW = CB / NW;  // waves; channels a wave stages
   constexpr int PAD = (KS - 1) / 2, TAPS = KS * KS;
   constexpr int NKS = CB / 2 / WK;           // channel pairs of a stage per wave
   constexpr int SEG = KS == 3 ? TAPS : 4, PPS = KS == 3 ? NKS : NKS / SEG, RING = KS == 3 ? 3 : 2;
@@ -78,11 +79,11 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 3 : 2) void fast_conv3d(F32Args
   // is read from the other
   __shared__ float buf0[CB * PITCH];
   __shared__ float buf1[CB * PITCH];
-  __shared__ float red[WK > 1 ? (WK - 1) * 4 * 64 * 16 : 1];
+  __shared__ float red[WK > 1 ? (WK - 1) * PXW * 64 * 16 : 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wpx = wave & 3, wk = wave >> 2;
+  const int wpx = wave % PXW, wk = wave / PXW;
   const int j = lane & 31, hi = lane >> 5;
 
   // workgroup -> tile, XCD-contiguous: output-channel tiles and output frames
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 3 : 2) void fast_conv3d(F32Args
     const int p = tid & (F_NPX - 1), row = p / a.bw, col = p - row * a.bw;
     const int h = h0 + row, w = w0 + col;
     if (row >= a.bh || h >= a.H || w >= a.W) return;
-    for (int cl = tid / F_NPX; cl < CB && c.c0 + cl < a.Ci; cl += 2 * WK)
+    for (int cl = tid / F_NPX; cl < CB && c.c0 + cl < a.Ci; cl += 2 * WK)  // 64 PXW WK threads
       a.cache_out[((static_cast<int64_t>(n) * a.Ci + c.c0 + cl) * a.L + (f - (a.Z - a.L))) * a.hw +
                   static_cast<int64_t>(h) * a.W + w] = buf[cl * PITCH + (row + PAD) * TW + col + PAD];
   };
@@ -254,13 +255,13 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 3 : 2) void fast_conv3d(F32Args
   if constexpr (WK > 1) {
     if (wk > 0)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[(((wk - 1) * 4 + wpx) * 16 + r) * 64 + lane] = acc[r];
+      for (int r = 0; r < 16; ++r) red[(((wk - 1) * PXW + wpx) * 16 + r) * 64 + lane] = acc[r];
     __syncthreads();
     if (wk > 0) return;
 #pragma unroll
     for (int q = 0; q + 1 < WK; ++q)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] += red[((q * 4 + wpx) * 16 + r) * 64 + lane];
+      for (int r = 0; r < 16; ++r) acc[r] += red[((q * PXW + wpx) * 16 + r) * 64 + lane];
   }
 
   // epilogue: bias once, NCTHW store (32 consecutive pixels of a channel)
@@ -275,11 +276,37 @@ __global__ __launch_bounds__(256 * WK, WK == 1 ? 3 : 2) void fast_conv3d(F32Args
   }
 }
 
-template <int KS, int CB, int NR>
-void launch_wk(int wk, const F32Args& a, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>(a.nblocks)), block(static_cast<unsigned>(256 * wk));
-  if (wk == 2) hipLaunchKernelGGL((fast_conv3d<KS, CB, NR, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((fast_conv3d<KS, CB, NR, 1>), grid, block, 0, s, a);
+template <int KS, int CB, int NR, int PXW, int WK>
+void launch_wk(const F32Args& a, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(a.nblocks)), block(64 * PXW * WK);
+  hipLaunchKernelGGL((fast_conv3d<KS, CB, NR, PXW, WK>), grid, block, 0, s, a);
+}
+
+// Tile shape: the fewest tiles of at most npx pixels (the frame's width in
+// equal columns, as many rows as fit), the widest on a tie; the halo tile of
+// a 3x3 kernel holds at most halo floats.  60x104, 128 pixels: 10 x 5 tiles
+// of 6 x 21 pixels (97% useful), where 4 x 64 tiles were 81%.
+void shape(F32Args* a, bool one, int npx, int halo) {
+  int64_t best = -1;
+  int prev = 0;
+  a->bh = a->bw = 1;
+  for (int c = a->W < npx ? a->W : npx; c >= 1 && (best < 0 || c >= npx / 16); --c) {
+    const int nt = (a->W + c - 1) / c, bw = (a->W + nt - 1) / nt;
+    if (nt == prev) continue;
+    prev = nt;
+    int bh = npx / bw < a->H ? npx / bw : a->H;
+    if (!one && bh > halo / (bw + 2) - 2) bh = halo / (bw + 2) - 2;
+    if (bh < 1) continue;
+    const int64_t tiles = static_cast<int64_t>((a->H + bh - 1) / bh) * nt;
+    if (best < 0 || tiles < best) {
+      best = tiles;
+      a->bh = bh;
+      a->bw = bw;
+    }
+    if (one) break;
+  }
+  a->tiles_w = (a->W + a->bw - 1) / a->bw;
+  a->tiles_h = (a->H + a->bh - 1) / a->bh;
 }
 
 // Every frame of the new cache is the source of some (output frame, last tap)
@@ -326,31 +353,17 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
   a.write_cache = (g.L > 0 && cache_covered(g)) ? 1 : 0;
   *cache_written = a.write_cache != 0;
 
-  // Tile shape: the fewest 128-pixel tiles (the frame's width in equal
-  // columns, as many rows as fit), the widest on a tie; the halo tile of a
-  // 3x3 kernel holds at most 256 floats.  60x104: 10 x 5 tiles of 6 x 21
-  // pixels (97% useful), where 4 x 64 tiles were 81%.
-  int64_t best = -1;
-  int prev = 0;
-  a.bh = a.bw = 1;
-  for (int c = a.W < F_NPX ? a.W : F_NPX; c >= 1 && (best < 0 || c >= 8); --c) {
-    const int nt = (a.W + c - 1) / c, bw = (a.W + nt - 1) / nt;
-    if (nt == prev) continue;
-    prev = nt;
-    int bh = F_NPX / bw < a.H ? F_NPX / bw : a.H;
-    if (!one && bh > 256 / (bw + 2) - 2) bh = 256 / (bw + 2) - 2;
-    if (bh < 1) continue;
-    const int64_t tiles = static_cast<int64_t>((a.H + bh - 1) / bh) * nt;
-    if (best < 0 || tiles < best) {
-      best = tiles;
-      a.bh = bh;
-      a.bw = bw;
-    }
-    if (one) break;
-  }
-  a.tiles_w = (a.W + a.bw - 1) / a.bw;
-  a.tiles_h = (a.H + a.bh - 1) / a.bh;
-  const int64_t blocks = static_cast<int64_t>(a.tiles_w) * a.tiles_h * p.cofrags * g.To * d.N;
+  auto blocks_of = [&]() { return static_cast<int64_t>(a.tiles_w) * a.tiles_h * p.cofrags * g.To * d.N; };
+  shape(&a, one, 128, 256);
+  // 32-pixel tiles, four waves along the channels, for a launch whose
+  // 128-pixel tiles leave half of the compute units idle: a quarter of the
+  // serial chain a wave and four times the workgroups (560 -> 48 at 40x56, two
+  // frames: 0.326 -> 0.179 ms; 48 -> 32 at 29x32: 0.036 -> 0.024).  Up to 32
+  // channels that chain is too short to be worth the extra halo: 32 -> 32 at
+  // 32x32 takes as long as its launch on either tile.
+  const bool small = d.Ci > 32 && blocks_of() <= device_compute_units() / 2;
+  if (small) shape(&a, one, 32, 64);
+  const int64_t blocks = blocks_of();
   if (info) {
     info->kernel = C3C_KERNEL_FAST_F32;
     info->tile_co = F_CO;
@@ -368,9 +381,16 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
   // another to switch to (384 -> 384 at 30x52, one frame, 156 workgroups: 0.224
   // ms, 0.237 unsplit; 192 -> 192 at 60x104, four frames, 1200 workgroups:
   // 0.479, 0.462 unsplit).  Four waves were slower than two (0.25, 0.58 ms).
-  const int wk = blocks <= 2 * device_compute_units() ? 2 : 1;
-  if (one) launch_wk<1, 32, 2>(wk, a, s);
-  else launch_wk<3, 16, 4>(wk, a, s);
+  const bool two = blocks <= 2 * device_compute_units();
+  if (one) {
+    if (small) launch_wk<1, 32, 1, 1, 4>(a, s);
+    else if (two) launch_wk<1, 32, 2, 4, 2>(a, s);
+    else launch_wk<1, 32, 2, 4, 1>(a, s);
+  } else {
+    if (small) launch_wk<3, 32, 1, 1, 4>(a, s);
+    else if (two) launch_wk<3, 16, 4, 4, 2>(a, s);
+    else launch_wk<3, 16, 4, 4, 1>(a, s);
+  }
   return hipGetLastError();
 }
 

@@ -34,6 +34,12 @@ CASES = [
     dict(Ci=20, Co=36, T=2, Tc=2, H=7, W=9, Kt=5, p_base=4),
     dict(Ci=12, Co=20, T=3, Tc=2, H=6, W=35, p_r=1),
     dict(Ci=19, Co=20, T=3, H=6, W=35, Kt=1),              # one temporal tap: no cache
+    # more than 32 channels, few workgroups: 32-pixel tiles
+    dict(Ci=33, Co=33, T=2, Tc=2, H=9, W=1),
+    dict(Ci=65, Co=40, T=1, Tc=0, H=1, W=67),
+    dict(N=2, Ci=63, Co=31, T=2, Tc=1, H=13, W=17),
+    dict(Ci=97, Co=64, T=3, Tc=2, H=31, W=33, p_r=1),
+    dict(Ci=34, Co=20, T=2, Tc=2, H=6, W=5, Kt=5, p_base=4),
     # 1x1: the plane as one row, temporal strides (the copy writes the cache)
     dict(Ci=31, Co=33, T=3, Tc=2, H=5, W=7, Kh=1, Kw=1),
     dict(Ci=64, Co=32, T=2, Tc=2, H=11, W=129, Kh=1, Kw=1),
