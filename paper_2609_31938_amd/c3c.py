@@ -13,6 +13,7 @@ p_h p_w groups has_bias``); element types are ``"bf16" "f32" "f16"``.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 import re
 
@@ -114,17 +115,13 @@ def declared_symbols():
     return sorted(set(re.findall(r"^\s*(?:int|const char\*)\s+(c3c_\w+)\s*\(", text, re.M)))
 
 
+# the spec's keys in the order of Desc's int64 fields
+_SPEC_VALUES = operator.itemgetter("N", "Ci", "Co", "T", "Tc", "H", "W", "Kt", "Kh", "Kw", "s_t", "s_h", "s_w",
+                                   "d_t", "d_h", "d_w", "p_base", "p_r", "p_h", "p_w", "groups")
+
+
 def make_desc(spec: dict, dtype: str) -> Desc:
-    d = Desc()
-    d.N, d.Ci, d.Co, d.T, d.Tc = spec["N"], spec["Ci"], spec["Co"], spec["T"], spec["Tc"]
-    d.H, d.W, d.Kt, d.Kh, d.Kw = spec["H"], spec["W"], spec["Kt"], spec["Kh"], spec["Kw"]
-    d.stride_t, d.stride_h, d.stride_w = spec["s_t"], spec["s_h"], spec["s_w"]
-    d.dil_t, d.dil_h, d.dil_w = spec["d_t"], spec["d_h"], spec["d_w"]
-    d.pad_t_base, d.pad_t_right = spec["p_base"], spec["p_r"]
-    d.pad_h, d.pad_w, d.groups = spec["p_h"], spec["p_w"], spec["groups"]
-    d.dtype = DTYPES[dtype]
-    d.has_bias = int(spec["has_bias"])
-    return d
+    return Desc(*_SPEC_VALUES(spec), DTYPES[dtype], int(spec["has_bias"]))
 
 
 def _raise(status, ctx=None, what=""):
@@ -209,11 +206,15 @@ class Context:
 
 # ---------------------------------------------------------------- host maths
 
-def output_dims(spec: dict, dtype: str = "bf16"):
-    v = [_i64() for _ in range(4)]
-    _raise(lib.c3c_output_dims(C.byref(make_desc(spec, dtype)), *[C.byref(x) for x in v]),
+def _output_dims(d: Desc):
+    to, ho, wo, n = _i64(), _i64(), _i64(), _i64()
+    _raise(lib.c3c_output_dims(C.byref(d), C.byref(to), C.byref(ho), C.byref(wo), C.byref(n)),
            what="c3c_output_dims")
-    return tuple(int(x.value) for x in v)
+    return to.value, ho.value, wo.value, n.value
+
+
+def output_dims(spec: dict, dtype: str = "bf16"):
+    return _output_dims(make_desc(spec, dtype))
 
 
 def tap_interval(spec: dict, k: int, dtype: str = "bf16"):
@@ -250,11 +251,14 @@ def plan_query(ctx, spec: dict, dtype: str, ws_bytes: int = 0) -> dict:
                 workgroups=p.workgroups, cache_in_kernel=bool(p.cache_in_kernel))
 
 
-def weight_pack_bytes(spec: dict, dtype: str) -> int:
+def _weight_pack_bytes(d: Desc) -> int:
     n = C.c_size_t()
-    _raise(lib.c3c_weight_pack_bytes(C.byref(make_desc(spec, dtype)), C.byref(n)),
-           what="c3c_weight_pack_bytes")
-    return int(n.value)
+    _raise(lib.c3c_weight_pack_bytes(C.byref(d), C.byref(n)), what="c3c_weight_pack_bytes")
+    return n.value
+
+
+def weight_pack_bytes(spec: dict, dtype: str) -> int:
+    return _weight_pack_bytes(make_desc(spec, dtype))
 
 
 def workspace_bytes(spec: dict, dtype: str) -> int:
@@ -289,13 +293,17 @@ _TORCH = {}
 
 
 def _torch_dtype(dtype):
-    import torch
-    return {"bf16": torch.bfloat16, "f32": torch.float32, "f16": torch.float16}[dtype]
+    if not _TORCH:
+        import torch
+        _TORCH.update(bf16=torch.bfloat16, f32=torch.float32, f16=torch.float16)
+    return _TORCH[dtype]
 
 
 def dtype_of(t) -> str:
-    import torch
-    return {torch.bfloat16: "bf16", torch.float32: "f32", torch.float16: "f16"}[t.dtype]
+    for name in ("bf16", "f32", "f16"):
+        if t.dtype == _torch_dtype(name):
+            return name
+    raise KeyError(t.dtype)
 
 
 def _check(t, name, dtype, numel=None):
@@ -317,21 +325,30 @@ def _ptr(t, name, dtype, numel=None):
     if t is None:
         return None
     _check(t, name, dtype, numel)
+    return _addr(t, name)
+
+
+def _addr(t, name):
+    if t is None:
+        return None
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     return t.data_ptr() or None
 
 
-def _sizes(spec: dict, dtype: str):
+def _sizes(spec: dict, dtype: str, d: Desc, dims):
     """Element counts of every tensor of a call: x, cache, w, wpack (0 when
-    the call has no fast layout), bias, y, cache_out."""
-    To, Ho, Wo, L = output_dims(spec, dtype)
+    the call has no fast layout), bias, y, cache_out.  A call makes its
+    descriptor and its output dimensions once and passes them around: made
+    anew by every helper, they were most of the 21 us that a small call took
+    on the host."""
+    To, Ho, Wo, L = dims
     hw = spec["H"] * spec["W"]
     nci = spec["N"] * spec["Ci"]
     es = 4 if dtype == "f32" else 2
     return dict(x=nci * spec["T"] * hw, cache=nci * spec["Tc"] * hw,
                 w=spec["Co"] * (spec["Ci"] // spec["groups"]) * spec["Kt"] * spec["Kh"] * spec["Kw"],
-                wpack=weight_pack_bytes(spec, dtype) // es, bias=spec["Co"],
+                wpack=_weight_pack_bytes(d) // es, bias=spec["Co"],
                 y=spec["N"] * spec["Co"] * To * Ho * Wo, cache_out=nci * L * hw)
 
 
@@ -375,16 +392,17 @@ def conv3d_causal_cached(ctx, spec: dict, x, cache, w, wpack, bias, y=None, cach
     outputs with torch when they are not given."""
     import torch
     dtype = dtype_of(w)
-    To, Ho, Wo, L = output_dims(spec, dtype)
+    desc = make_desc(spec, dtype)
+    dims = To, Ho, Wo, L = _output_dims(desc)
     dev = w.device
     if y is None:
         y = torch.empty((spec["N"], spec["Co"], To, Ho, Wo), dtype=w.dtype, device=dev)
     if cache_out is None:
         cache_out = torch.empty((spec["N"], spec["Ci"], L, spec["H"], spec["W"]),
                                 dtype=w.dtype, device=dev)
-    n = _sizes(spec, dtype)
+    n = _sizes(spec, dtype, desc, dims)
     st = lib.c3c_conv3d_causal_cached(
-        ctx._h, C.byref(make_desc(spec, dtype)), *_call_ptrs(spec, dtype, n, x, cache, w, wpack,
+        ctx._h, C.byref(desc), *_call_ptrs(spec, dtype, n, x, cache, w, wpack,
                                                             bias, y, cache_out),
         _stream(stream))
     _raise(st, ctx, "c3c_conv3d_causal_cached")
@@ -398,11 +416,12 @@ def conv3d_causal_cached_noalloc(ctx, spec: dict, x, cache, w, wpack, bias, y, c
     scratch.  The caller passes every output; nothing is allocated here or in
     the library.  Returns (y, cache_out)."""
     dtype = dtype_of(w)
-    n = _sizes(spec, dtype)
+    desc = make_desc(spec, dtype)
+    n = _sizes(spec, dtype, desc, _output_dims(desc))
     if y is None or (cache_out is None and n["cache_out"] > 0):
         raise ValueError("the allocation-free call takes caller-allocated y and cache_out")
     st = lib.c3c_conv3d_causal_cached_noalloc(
-        ctx._h, C.byref(make_desc(spec, dtype)), *_call_ptrs(spec, dtype, n, x, cache, w, wpack,
+        ctx._h, C.byref(desc), *_call_ptrs(spec, dtype, n, x, cache, w, wpack,
                                                             bias, y, cache_out),
         _stream(stream))
     _raise(st, ctx, "c3c_conv3d_causal_cached_noalloc")
@@ -416,17 +435,12 @@ def _call_ptrs(spec, dtype, n, x, cache, w, wpack, bias, y, cache_out):
     where the call does not route fast (the library then rejects it)."""
     if wpack is not None and n["wpack"] == 0:
         raise ValueError("wpack given, but this call has no fast-route weight layout")
-    for t, name in ((x, "x"), (cache if spec["Tc"] else None, "cache"), (w, "w"),
-                    (wpack, "wpack"), (bias if spec["has_bias"] else None, "bias"), (y, "y"),
-                    (cache_out, "cache_out")):
+    tensors = ((x, "x"), (cache if spec["Tc"] else None, "cache"), (w, "w"),
+               (wpack, "wpack"), (bias if spec["has_bias"] else None, "bias"), (y, "y"),
+               (cache_out, "cache_out"))
+    for t, name in tensors:
         _check(t, name, dtype, n[name])
-    return (_ptr(x, "x", dtype, n["x"]),
-            _ptr(cache, "cache", dtype, n["cache"]) if spec["Tc"] else None,
-            _ptr(w, "w", dtype, n["w"]),
-            _ptr(wpack, "wpack", dtype, n["wpack"]),
-            _ptr(bias, "bias", dtype, n["bias"]) if spec["has_bias"] else None,
-            _ptr(y, "y", dtype, n["y"]),
-            _ptr(cache_out, "cache_out", dtype, n["cache_out"]))
+    return [_addr(t, name) for t, name in tensors]
 
 
 def conv3d_causal_cached_fused(ctx, spec: dict, x, cache, w, wpack, bias, scale=None, shift=None,
@@ -437,7 +451,8 @@ def conv3d_causal_cached_fused(ctx, spec: dict, x, cache, w, wpack, bias, scale=
     ``residual`` may be ``y`` itself.  Returns (y, cache_out)."""
     import torch
     dtype = dtype_of(w)
-    To, Ho, Wo, L = output_dims(spec, dtype)
+    desc = make_desc(spec, dtype)
+    dims = To, Ho, Wo, L = _output_dims(desc)
     dev = w.device
     if y is None:
         y = torch.empty((spec["N"], spec["Co"], To, Ho, Wo), dtype=w.dtype, device=dev)
@@ -445,13 +460,13 @@ def conv3d_causal_cached_fused(ctx, spec: dict, x, cache, w, wpack, bias, scale=
         cache_out = torch.empty((spec["N"], spec["Ci"], L, spec["H"], spec["W"]),
                                 dtype=w.dtype, device=dev)
     nc = spec["N"] * spec["Ci"]
-    n = _sizes(spec, dtype)
+    n = _sizes(spec, dtype, desc, dims)
     _check(scale, "scale", "f32", nc)
     _check(shift, "shift", "f32", nc)
     _check(residual, "residual", dtype, n["y"])
     px, pc, pw, pp, pb, py, po = _call_ptrs(spec, dtype, n, x, cache, w, wpack, bias, y, cache_out)
     st = lib.c3c_conv3d_causal_cached_fused(
-        ctx._h, C.byref(make_desc(spec, dtype)), px, pc, pw, pp, pb,
+        ctx._h, C.byref(desc), px, pc, pw, pp, pb,
         _ptr(scale, "scale", "f32", nc), _ptr(shift, "shift", "f32", nc),
         _ptr(residual, "residual", dtype, n["y"]), py, po, _stream(stream))
     _raise(st, ctx, "c3c_conv3d_causal_cached_fused")
@@ -468,20 +483,21 @@ def conv3d_causal_cached_block(ctx, spec: dict, x, cache, w, wpack, bias, gamma,
     (y, cache_out)."""
     import torch
     dtype = dtype_of(w)
-    To, Ho, Wo, L = output_dims(spec, dtype)
+    desc = make_desc(spec, dtype)
+    dims = To, Ho, Wo, L = _output_dims(desc)
     dev = w.device
     if y is None:
         y = torch.empty((spec["N"], spec["Co"], To, Ho, Wo), dtype=w.dtype, device=dev)
     if cache_out is None:
         cache_out = torch.empty((spec["N"], spec["Ci"], L, spec["H"], spec["W"]),
                                 dtype=w.dtype, device=dev)
-    n = _sizes(spec, dtype)
+    n = _sizes(spec, dtype, desc, dims)
     _check(gamma, "gamma", "f32", spec["Ci"])
     _check(beta, "beta", "f32", spec["Ci"])
     _check(residual, "residual", dtype, n["y"])
     px, pc, pw, pp, pb, py, po = _call_ptrs(spec, dtype, n, x, cache, w, wpack, bias, y, cache_out)
     st = lib.c3c_conv3d_causal_cached_block(
-        ctx._h, C.byref(make_desc(spec, dtype)), px, pc, pw, pp, pb,
+        ctx._h, C.byref(desc), px, pc, pw, pp, pb,
         _ptr(gamma, "gamma", "f32", spec["Ci"]), _ptr(beta, "beta", "f32", spec["Ci"]),
         float(eps), _ptr(residual, "residual", dtype, n["y"]), py, po, _stream(stream))
     _raise(st, ctx, "c3c_conv3d_causal_cached_block")
