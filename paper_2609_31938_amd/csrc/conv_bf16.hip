@@ -733,7 +733,7 @@ __global__ __launch_bounds__(256) void splitk_reduce(const float* __restrict__ p
 }
 
 // Tile configurations of the bf16 kernel (template arguments of run()).
-enum Cfg { CFG_C192, CFG_C96, CFG_C16, CFG_C160_4X80, CFG_C160_10X32, CFG_C128_4X80, CFG_C128_10X32, CFG_C64_4X64 };
+enum Cfg { CFG_C192, CFG_C96, CFG_C48, CFG_C32, CFG_C16, CFG_C160_4X80, CFG_C160_10X32, CFG_C128_4X80, CFG_C128_10X32, CFG_C64_4X64 };
 
 // Launch plan of one bf16 fast call: tile configuration, workgroups of one
 // split, split-K factor, and the fp32 partial-sum bytes the split needs.
@@ -856,6 +856,15 @@ Plan plan_bf16(const Geo& g) {
     // 96-channel tile
     p.cfg = CFG_C16;
     set_tiles(g, 16, 8, 64, &p);
+  } else if (Co <= 48) {
+    // 32 or 48 channels x 8 x 64 pixels on four waves of 2 rows: a 96-channel
+    // tile would spend half or two thirds of its products on padding (1x3x3,
+    // 64 -> 32 at 533x610: 62 us against 49 here; the 48 -> 48 block form at
+    // 450x846, two frames: 419 against 374; 304 -> 48 at 107x210: 104 against
+    // 93).  Above 48 a 64-channel tile of this shape would do as many products
+    // per LDS read and 12% fewer in all.
+    p.cfg = Co <= 32 ? CFG_C32 : CFG_C48;
+    set_tiles(g, Co <= 32 ? 32 : 48, 8, 64, &p);
   } else if (Co <= 96) {
     // 96 channels x 6 x 64 pixels on 2 x 2 waves (48 channels x 3 rows each):
     // each weight fragment is fetched by two waves, not four, and the smaller
@@ -900,6 +909,17 @@ Plan plan_bf16(const Geo& g) {
         ((r2.blocks + cus - 1) / cus) * 128 < ((p.blocks + cus - 1) / cus) * pco) {
       p = r2;
       p.cfg = CFG_C128_10X32;
+    }
+    // 192-channel 4 x 64 tiles when they pad fewer output channels (176: 192
+    // against 256; 528: 576 against 640) and take less time in whole rounds
+    // (64 -> 176 at 240x416, four frames: 0.251 ms, 0.334 on 128 channels;
+    // 176 -> 176 at 352x640, two frames: 0.674, 0.875)
+    Plan r3;
+    set_tiles(g, 192, 4, 64, &r3);
+    if (r3.tiles_co * 192 < p.tiles_co * (p.tile_flop_px / 320) &&
+        (r3.blocks + cus - 1) / cus * r3.tile_flop_px < (p.blocks + cus - 1) / cus * p.tile_flop_px) {
+      p = r3;
+      p.cfg = CFG_C192;
     }
   }
   p.splits = 1;
@@ -1044,6 +1064,8 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
   switch (pl.cfg) {
     case CFG_C192: return run<6, 2, 4, 2, 2, 3>(g, a, pl, aligned, fused, s, info);
     case CFG_C96: return run<3, 3, 4, 2, 2, 3>(g, a, pl, aligned, fused, s, info);
+    case CFG_C48: return run<3, 2, 4, 1, 4, 2>(g, a, pl, aligned, fused, s, info);
+    case CFG_C32: return run<2, 2, 4, 1, 4, 2>(g, a, pl, aligned, fused, s, info);
     case CFG_C16: return run<1, 2, 4, 1, 4, 2>(g, a, pl, aligned, fused, s, info);
     // two LDS buffers measured 1.4-3.4% faster than three on the 720p
     // layers for this tile (the 192- and 96-channel tiles keep three)

@@ -20,12 +20,15 @@ PIN = c3c.MODE_CHANNEL_TILES
 # (mode, tile, shape): every tile of the 3x3 kernel
 TILES = [
     (PIN, (16, 8, 64), dict(Co=12, H=11, W=72)),
+    (0, (32, 8, 64), dict(Co=20, H=11, W=72)),
+    (0, (48, 8, 64), dict(Co=41, H=17, W=136)),
     (0, (96, 6, 64), dict(Co=90, H=9, W=72)),
     (PIN, (128, 4, 80), dict(Co=256, H=9, W=88)),
     (PIN, (128, 10, 32), dict(Co=256, T=4, H=153, W=40)),
     (PIN, (160, 4, 80), dict(Co=150, H=9, W=88)),
     (PIN, (160, 10, 32), dict(Co=150, T=4, H=333, W=32)),
     (PIN, (192, 4, 64), dict(Co=192, H=9, W=72)),
+    (0, (192, 4, 64), dict(Co=528, T=4, H=65, W=64)),
     (0, (64, 4, 64), dict(Co=192, H=9, W=72)),
     # one frame a source: the element after the last real channel is the
     # first of the padding channels (NaN here), and must not be read as one
