@@ -138,6 +138,12 @@ CASES = [
     (dict(N=1, Ci=384, Co=384, T=1, Tc=2, H=12, W=26), "conv3d_bf16"),    # split-K in the workspace
     (dict(N=1, Ci=160, Co=160, T=2, Tc=2, H=8, W=80), "conv3d_bf16"),     # pass: 12 rows per lane
     (dict(N=1, Ci=400, Co=32, T=1, Tc=2, H=6, W=16), "conv3d_bf16"),      # pass: > 384 channels, loop
+    # the pass on odd planes: 6, 12 and 24 rows per lane and the loop, a plane
+    # of less than one run, several tiles of 128 pixels
+    (dict(N=2, Ci=33, Co=33, T=3, Tc=2, H=13, W=31), "conv3d_bf16"),
+    (dict(N=1, Ci=100, Co=64, T=2, Tc=2, H=1, W=5), "conv3d_bf16"),
+    (dict(N=1, Ci=200, Co=32, T=2, Tc=1, H=11, W=25), "conv3d_bf16"),
+    (dict(N=1, Ci=390, Co=32, T=2, Tc=2, H=7, W=19), "conv3d_bf16"),
 ]
 
 
