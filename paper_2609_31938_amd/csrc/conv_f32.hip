@@ -358,11 +358,22 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
   // 32-pixel tiles, four waves along the channels, for a launch whose
   // 128-pixel tiles leave half of the compute units idle: a quarter of the
   // serial chain a wave and four times the workgroups (560 -> 48 at 40x56, two
-  // frames: 0.326 -> 0.179 ms; 48 -> 32 at 29x32: 0.036 -> 0.024).  Up to 32
-  // channels that chain is too short to be worth the extra halo: 32 -> 32 at
-  // 32x32 takes as long as its launch on either tile.
-  const bool small = d.Ci > 32 && blocks_of() <= device_compute_units() / 2;
-  if (small) shape(&a, one, 32, 64);
+  // frames: 0.326 -> 0.179 ms; 48 -> 32 at 29x32: 0.036 -> 0.024); or whose
+  // share of the busiest compute unit they cut by 18% or more, which is worth
+  // their larger halo (160 -> 400 at 27x48, two frames: 286 workgroups of 128,
+  // 0.166 ms, 1066 of 32, 0.115; 192 -> 128 at 56x112, four frames: 0.379,
+  // 0.328; with equal shares 128-pixel tiles win: 48 -> 336 at 48x60, 0.129,
+  // 0.139).  Up to 32 channels the chain is too short to matter and 128 pixels
+  // stay (32 -> 624 at 19x21, three frames: 0.027 ms on the first).
+  const int64_t cus = device_compute_units(), wide = blocks_of();
+  bool small = d.Ci > 32;
+  if (small) {
+    shape(&a, one, 32, 64);
+    // (their stages are 32 channels, the others' 16: a ragged last one weighs more)
+    const int64_t c32 = (d.Ci + 31) / 32 * 32, c16 = (d.Ci + 15) / 16 * 16;
+    small = wide <= cus / 2 || (blocks_of() + cus - 1) / cus * c32 * 100 <= (wide + cus - 1) / cus * 4 * c16 * 82;
+    if (!small) shape(&a, one, 128, 256);
+  }
   const int64_t blocks = blocks_of();
   if (info) {
     info->kernel = C3C_KERNEL_FAST_F32;
