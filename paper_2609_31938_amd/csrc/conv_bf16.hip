@@ -834,6 +834,15 @@ namespace {
 
 int64_t compute_units() { return device_compute_units(); }
 
+// Whether a call of at most 48 output channels takes its own narrow tile
+// rather than the 96-channel one (the reason stands in plan_bf16).
+bool narrow_pays(const Geo& g, int64_t cus) {
+  Plan n, w;
+  set_tiles(g, 48, 8, 64, &n);  // one output-channel tile at 32 channels too
+  set_tiles(g, 96, 6, 64, &w);
+  return g.d.W % 8 != 0 || (n.blocks + cus - 1) / cus < (w.blocks + cus - 1) / cus;
+}
+
 // The tile configuration by output-channel count, and the split-K factor: a
 // call whose workgroups fill less than one round of the compute units splits
 // each tile's stages over S workgroups when the modelled time (microseconds)
@@ -856,12 +865,15 @@ Plan plan_bf16(const Geo& g) {
     // 96-channel tile
     p.cfg = CFG_C16;
     set_tiles(g, 16, 8, 64, &p);
-  } else if (Co <= 48) {
+  } else if (Co <= 48 && narrow_pays(g, cus)) {
     // 32 or 48 channels x 8 x 64 pixels on four waves of 2 rows: a 96-channel
     // tile would spend half or two thirds of its products on padding (1x3x3,
     // 64 -> 32 at 533x610: 62 us against 49 here; the 48 -> 48 block form at
     // 450x846, two frames: 419 against 374; 304 -> 48 at 107x210: 104 against
-    // 93).  Above 48 a 64-channel tile of this shape would do as many products
+    // 93).  A workgroup's time is its staging's, two rows more than the
+    // 96-channel tile's, so with no fewer rounds of workgroups and no unaligned
+    // loads to shift the wide tile stays (400 -> 48 at 215x328, two frames: 333
+    // against 353).  Above 48 a 64-channel tile of this shape would do as many products
     // per LDS read and 12% fewer in all.
     p.cfg = Co <= 32 ? CFG_C32 : CFG_C48;
     set_tiles(g, Co <= 32 ? 32 : 48, 8, 64, &p);

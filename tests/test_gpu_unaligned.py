@@ -20,8 +20,8 @@ PIN = c3c.MODE_CHANNEL_TILES
 # (mode, tile, shape): every tile of the 3x3 kernel
 TILES = [
     (PIN, (16, 8, 64), dict(Co=12, H=11, W=72)),
-    (0, (32, 8, 64), dict(Co=20, H=11, W=72)),
-    (0, (48, 8, 64), dict(Co=41, H=17, W=136)),
+    (0, (32, 8, 64), dict(Co=20, T=6, H=95, W=136)),
+    (0, (48, 8, 64), dict(Co=41, T=6, H=95, W=136)),
     (0, (96, 6, 64), dict(Co=90, H=9, W=72)),
     (PIN, (128, 4, 80), dict(Co=256, H=9, W=88)),
     (PIN, (128, 10, 32), dict(Co=256, T=4, H=153, W=40)),
