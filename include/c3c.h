@@ -410,7 +410,9 @@ int c3c_conv3d_causal_cached_block(c3c_ctx* ctx, const c3c_conv_desc* d,
  * bytes of device memory on each device the library runs on, held until the
  * process ends.  The array is looked up on the call's first use of a device
  * (no allocation).  A call whose split needs more than that returns EINVAL
- * (not counted) with a message naming both sizes.  Every call on one device
+ * (not counted) with a message naming both sizes, unless the tiling that its
+ * output channels alone call for would need no more than that: it then runs
+ * unsplit.  Every call on one device
  * shares its array, which keeps the last call's partial sums: calls that
  * overlap in time on one device (several streams or host threads) race and
  * must be serialised by the caller.  The context's workspace, if any, is

@@ -547,7 +547,7 @@ int c3c_conv3d_causal_cached_noalloc(c3c_ctx* ctx, const c3c_conv_desc* d, const
   // the split-K bytes this call plans for, when it routes fast
   int64_t need = 0;
   if (decide(g, ctx->mode) == C3C_REASON_NONE && d->dtype == C3C_DTYPE_BF16 && spatial_3x3(*d))
-    need = fast_bf16_workspace_bytes(g);
+    need = fast_bf16_noalloc_bytes(g);
   if (need > kNoallocScratchBytes)
     return fail(ctx, C3C_E_INVAL,
                 "split-K needs " + std::to_string(need) + " bytes of scratch; the allocation-free "

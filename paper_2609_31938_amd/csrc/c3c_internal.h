@@ -91,6 +91,10 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
                            hipStream_t s, LaunchInfo* info = nullptr);
 // fp32 partial-sum bytes a bf16 fast call would split into (0: it runs unsplit)
 int64_t fast_bf16_workspace_bytes(const Geo& g);
+// the same for the allocation-free entry point, whose scratch is fixed: 0 also
+// for a call that would split into more than the scratch only because of a
+// tile taken for its whole rounds of workgroups (it runs unsplit)
+int64_t fast_bf16_noalloc_bytes(const Geo& g);
 // fallback, pointwise case (pointwise.hip): 1x1x1, unit spatial stride, no
 // spatial padding, one group, bf16 / fp16, 8-channel groups of aligned weights
 bool pointwise_eligible(const Geo& g, const void* x, const void* cache, const void* w, const void* y,

@@ -852,7 +852,9 @@ bool narrow_pays(const Geo& g, int64_t cus) {
 // 6.9 TFLOP/s per compute unit, the measured main-loop rate; 3 stages stand
 // for a workgroup's fixed cost; the last term is the fp32 partial sums
 // written and read back, and the reduction launch.
-Plan plan_bf16(const Geo& g) {
+// by_channels: the tiling by output channels alone, without the rules that
+// take another one for its whole rounds of workgroups.
+Plan plan_bf16(const Geo& g, bool by_channels = false) {
   Plan p;
   const int64_t Co = g.d.Co;
   const int64_t cus = compute_units();
@@ -865,7 +867,7 @@ Plan plan_bf16(const Geo& g) {
     // 96-channel tile
     p.cfg = CFG_C16;
     set_tiles(g, 16, 8, 64, &p);
-  } else if (Co <= 48 && narrow_pays(g, cus)) {
+  } else if (!by_channels && Co <= 48 && narrow_pays(g, cus)) {
     // 32 or 48 channels x 8 x 64 pixels on four waves of 2 rows: a 96-channel
     // tile would spend half or two thirds of its products on padding (1x3x3,
     // 64 -> 32 at 533x610: 62 us against 49 here; the 48 -> 48 block form at
@@ -917,7 +919,7 @@ Plan plan_bf16(const Geo& g) {
     Plan r2;
     set_tiles(g, 128, 10, 32, &r2);
     const int64_t pco = p.cfg == CFG_C128_4X80 ? 128 : 160;
-    if (r2.tiles_co * 128 <= p.tiles_co * pco &&
+    if (!by_channels && r2.tiles_co * 128 <= p.tiles_co * pco &&
         ((r2.blocks + cus - 1) / cus) * 128 < ((p.blocks + cus - 1) / cus) * pco) {
       p = r2;
       p.cfg = CFG_C128_10X32;
@@ -928,7 +930,7 @@ Plan plan_bf16(const Geo& g) {
     // 176 -> 176 at 352x640, two frames: 0.674, 0.875)
     Plan r3;
     set_tiles(g, 192, 4, 64, &r3);
-    if (r3.tiles_co * 192 < p.tiles_co * (p.tile_flop_px / 320) &&
+    if (!by_channels && r3.tiles_co * 192 < p.tiles_co * (p.tile_flop_px / 320) &&
         (r3.blocks + cus - 1) / cus * r3.tile_flop_px < (p.blocks + cus - 1) / cus * p.tile_flop_px) {
       p = r3;
       p.cfg = CFG_C192;
@@ -1018,6 +1020,16 @@ Plan unsplit_plan(const Geo& g, Plan p) {
 }  // namespace
 
 int64_t fast_bf16_workspace_bytes(const Geo& g) { return plan_bf16(g).part_bytes; }
+
+// A tile taken for its whole rounds of workgroups can bring a call below one
+// round and so to a split that the scratch does not hold, where the tiling by
+// channels alone splits into less or not at all: such a call runs unsplit on
+// its tile (400 -> 176 at 84x112, four frames: 0.167 ms, 0.161 split, 0.271 on
+// the tiling by channels; 1018 -> 704, 4x3x3 taps at 95x90: 0.513, 0.472, 0.943).
+int64_t fast_bf16_noalloc_bytes(const Geo& g) {
+  const int64_t need = plan_bf16(g).part_bytes;
+  return need > kNoallocScratchBytes && plan_bf16(g, true).part_bytes <= kNoallocScratchBytes ? 0 : need;
+}
 
 hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, const void* wpack,
                             const void* bias, void* y, void* cache_out, void* ws,

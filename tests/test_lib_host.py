@@ -521,6 +521,32 @@ def test_noalloc_refuses_an_oversized_split_before_device_work():
     assert ctx.counters()["failed"] == 1
 
 
+@no_gpu
+@pytest.mark.parametrize("over", [
+    # 192-channel tiles for whole rounds
+    dict(Ci=432, Co=176, T=3, Tc=2, H=105, W=112),
+    dict(Ci=400, Co=176, T=4, Tc=2, H=84, W=112),
+    dict(Ci=528, Co=176, T=4, Tc=2, H=83, W=116),
+    dict(N=2, Ci=767, Co=518, T=8, Tc=3, H=15, W=36, Kt=4),
+    # 128-channel 10 x 32 tiles for whole rounds
+    dict(Ci=1018, Co=704, T=1, Tc=3, H=95, W=90, Kt=4),
+    dict(Ci=529, Co=633, T=1, Tc=3, H=101, W=89, Kt=4),
+])
+def test_noalloc_runs_unsplit_where_only_the_tile_makes_the_split_too_large(over):
+    """A tile taken for its whole rounds of workgroups may split a call into
+    more than the scratch holds where the tiling by channels does not: the
+    allocation-free call is not refused for it (it reaches its launch, which
+    fails here only for want of a device)."""
+    sp = spec(**over)
+    assert c3c.workspace_bytes(sp, "bf16") > c3c.NOALLOC_SCRATCH_BYTES
+    ctx = c3c.Context()
+    p = FAKE
+    assert c3c.lib.c3c_conv3d_causal_cached_noalloc(
+        ctx._h, C.byref(c3c.make_desc(sp, "bf16")), p["x"], p["cache"], p["w"], p["wpack"], p["b"],
+        p["y"], p["co"], None) == c3c.E_DEVICE, ctx.last_error
+    assert ctx.counters()["failed"] == 1
+
+
 # ---------------------------------------------------------------- normalised block form
 def _block(ctx, sp, dtype="bf16", gamma=0x11000000, beta=0x12000000, eps=1e-6, res=None, **over):
     p = dict(FAKE)

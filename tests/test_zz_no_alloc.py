@@ -114,3 +114,21 @@ def test_noalloc_refuses_a_split_larger_than_the_scratch():
         c3c.conv3d_causal_cached_noalloc(ctx, sp, x, cache, w, wpack, b, y, co)
     assert e.value.status == c3c.E_INVAL and "scratch" in str(e.value)
     assert ctx.counters()["calls"] == 0
+
+
+def test_noalloc_runs_unsplit_where_only_the_tile_makes_the_split_too_large():
+    """528 -> 176 at 83x116 takes 192-channel tiles for whole rounds and would
+    split into more than the scratch: it runs unsplit, like the plain call
+    without a workspace, bit for bit."""
+    sp = spec(N=1, Ci=528, Co=176, T=4, Tc=2, H=83, W=116)
+    assert c3c.workspace_bytes(sp, "bf16") > c3c.NOALLOC_SCRATCH_BYTES
+    w, b, x, cache = _inputs(sp, 9)
+    ctx = c3c.Context()
+    wpack = c3c.weight_repack(ctx, sp, w)
+    say("noalloc call 528->176 83x116")
+    y_ref, c_ref = c3c.conv3d_causal_cached(ctx, sp, x, cache, w, wpack, b)
+    y, co = torch.empty_like(y_ref), torch.empty_like(c_ref)
+    c3c.conv3d_causal_cached_noalloc(ctx, sp, x, cache, w, wpack, b, y, co)
+    torch.cuda.synchronize()
+    assert torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+    assert torch.equal(co.view(torch.int16), c_ref.view(torch.int16))
