@@ -775,9 +775,12 @@ hipError_t run(const Geo& g, Args a, const Plan& p, bool aligned, int fused, hip
   a.nblocks = static_cast<int>(blocks);
   const dim3 grid(static_cast<unsigned>(blocks)), block(64 * WAVES_CO * WAVES_PX);
   const bool split = a.splits > 1;
+  // (the 32- and 48-channel tiles have no unaligned prologue instance: launch_fast_bf16)
+  constexpr bool NARROW = WAVES_CO == 1 && WCO > 1;
 #define C3C_BF16(AL, SP, FU)                                                                        \
-  if (aligned == AL && split == SP && fused == FU)                                                   \
-    hipLaunchKernelGGL((conv3d_bf16<WCO, WR, WCF, WAVES_CO, WAVES_PX, NBUF, AL, SP, FU>), grid, block, 0, s, a);
+  if constexpr (AL || FU != 2 || !NARROW)                                                            \
+    if (aligned == AL && split == SP && fused == FU)                                                 \
+      hipLaunchKernelGGL((conv3d_bf16<WCO, WR, WCF, WAVES_CO, WAVES_PX, NBUF, AL, SP, FU>), grid, block, 0, s, a);
   C3C_BF16(true, false, 0) C3C_BF16(false, false, 0) C3C_BF16(true, true, 0) C3C_BF16(false, true, 0)
   C3C_BF16(true, false, 1) C3C_BF16(false, false, 1) C3C_BF16(true, true, 1) C3C_BF16(false, true, 1)
   C3C_BF16(true, false, 2) C3C_BF16(false, false, 2) C3C_BF16(true, true, 2) C3C_BF16(false, true, 2)
@@ -1078,7 +1081,13 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
                        (cache == nullptr || aligned16(cache)) &&
                        (cache_out == nullptr || aligned16(cache_out)) &&
                        (fu.residual == nullptr || (reinterpret_cast<uintptr_t>(fu.residual) & 7u) == 0);
-  Plan pl = plan_bf16(g);
+  // A prologue in the kernel over unaligned tensors keeps the 96-channel tile:
+  // a 32- or 48-channel one stages 320 segments with 256 threads, so that every
+  // thread shifts, activates and masks two, and its registers overflow to
+  // scratch memory (160 -> 40 at 224x277, four frames: 1.062 ms, 0.311 on the
+  // 96-channel tile; 32 -> 48 at 87x171: 0.090, 0.040).
+  const bool by_channels = fused == 2 && !aligned && g.d.Co <= 48;
+  Plan pl = plan_bf16(g, by_channels);
   // split-K only with a large enough, 16-byte-aligned workspace; else unsplit
   const bool split = pl.splits > 1 && ws != nullptr && ws_bytes >= pl.part_bytes &&
                      (reinterpret_cast<uintptr_t>(ws) & 15u) == 0;

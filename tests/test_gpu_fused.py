@@ -131,6 +131,20 @@ def test_fused_parts_and_in_place(pro, res, inplace, mode):
          inplace=inplace, expect_fast=True)
 
 
+# An unaligned prologue of 17 to 48 output channels runs on the 96-channel tile
+# also where the plain call takes a narrow one (252 workgroups, one round).
+@pytest.mark.parametrize("over,tile_co", [(dict(Ci=24, Co=40, T=1, Tc=2, H=282, W=415), 48),
+                                          (dict(Ci=40, Co=24, T=1, Tc=2, H=281, W=413), 32)])
+def test_unaligned_prologue_with_few_output_channels(over, tile_co):
+    sp = spec(**over)
+    assert c3c.plan_query(None, sp, "bf16")["tile_co"] == tile_co
+    _run(sp, expect_fast=True)
+
+
+def test_unaligned_prologue_with_few_output_channels_split():
+    _run(spec(Ci=256, Co=40, T=1, Tc=2, H=19, W=27), ws=True, expect_fast=True)
+
+
 @pytest.mark.parametrize("over", [dict(N=1, Ci=128, Co=128, T=1, Tc=2, H=16, W=32),
                                   dict(N=1, Ci=128, Co=96, T=1, Tc=2, H=30, W=40)])
 @pytest.mark.parametrize("inplace", [False, True])

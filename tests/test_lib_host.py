@@ -547,6 +547,52 @@ def test_noalloc_runs_unsplit_where_only_the_tile_makes_the_split_too_large(over
     assert ctx.counters()["failed"] == 1
 
 
+def _kernels():
+    """The metadata of every gfx950 kernel in the built library: name -> the
+    compiler's record (code objects sit in offload bundles, their metadata in a
+    note of type 32)."""
+    import struct
+    import msgpack
+    with open(c3c.lib._name, "rb") as f:
+        b = f.read()
+    out, magic = {}, b"__CLANG_OFFLOAD_BUNDLE__"
+    at = b.find(magic)
+    while at >= 0:
+        n, = struct.unpack_from("<Q", b, at + 24)
+        q = at + 32
+        for _ in range(n):
+            off, size, tl = struct.unpack_from("<QQQ", b, q)
+            target = b[q + 24:q + 24 + tl]
+            q += 24 + tl
+            if b"gfx950" not in target:
+                continue
+            e = b[at + off:at + off + size]
+            phoff, = struct.unpack_from("<Q", e, 32)
+            phsize, phnum = struct.unpack_from("<HH", e, 54)
+            for i in range(phnum):
+                kind, _, r = struct.unpack_from("<IIQ", e, phoff + i * phsize)
+                end = r + struct.unpack_from("<Q", e, phoff + i * phsize + 32)[0]
+                while kind == 4 and r < end:
+                    ns, ds, nt = struct.unpack_from("<III", e, r)
+                    d = r + 12 + (ns + 3) // 4 * 4
+                    if nt == 32:
+                        out.update((k[".name"], k) for k in msgpack.unpackb(e[d:d + ds])["amdhsa.kernels"])
+                    r = d + (ds + 3) // 4 * 4
+        at = b.find(magic, at + 1)
+    return out
+
+
+def test_narrow_tiles_keep_their_registers():
+    """No instance of the bf16 3x3 kernel's 32- and 48-channel tiles holds a
+    staged register in scratch memory (an unaligned prologue instance did, and
+    took twice the time of the 96-channel tile)."""
+    names = {n: k for n, k in _kernels().items()
+             if "conv3d_bf16ILi2ELi2ELi4ELi1E" in n or "conv3d_bf16ILi3ELi2ELi4ELi1E" in n}
+    assert len(names) == 20  # two tiles, ten of the twelve forms each
+    for n, k in names.items():
+        assert k[".private_segment_fixed_size"] == 0, n
+
+
 # ---------------------------------------------------------------- normalised block form
 def _block(ctx, sp, dtype="bf16", gamma=0x11000000, beta=0x12000000, eps=1e-6, res=None, **over):
     p = dict(FAKE)
