@@ -44,6 +44,7 @@
 //     output frames of the same spatial tile, then neighbouring tiles -- so
 //     the frames shared by neighbouring taps and the halos are L2 hits.
 #include <atomic>
+#include <type_traits>
 
 #include "c3c_internal.h"
 #include "fuse_dev.h"
@@ -629,33 +630,47 @@ __global__ __launch_bounds__(64 * WAVES_CO * WAVES_PX, 1) void conv3d_bf16(Args 
   uint16_t* ybase = a.y + (static_cast<int64_t>(n) * a.Co) * plane + static_cast<int64_t>(o) * a.hw;
   // RES: every fragment's residual values, loaded as one batch before any
   // store (branch-free: a position outside the output reads the residual's
-  // first element and is not used), so the block waits for memory once
+  // first element and is not used), so the block waits for memory once.
+  // Unaligned: 8 bytes at any 2-byte alignment, a position among the tensor's
+  // last three elements from its last 8 bytes, shifted (a branch there had every
+  // fragment wait for its own loads: 16 -> 24, 1x3x3 at 175x249, two frames, 19.7 us
+  // on the 96-channel tile, 14.6 now); a tensor of fewer than four elements one by one.
   if constexpr (FU != 0 || !ALIGNED) load_bias();
   uint2 rv[RES ? WCO : 1][RES ? NPF : 1];
   if constexpr (RES) {
     const bool has_r = a.residual != nullptr;
+    const uint16_t* rsrc = has_r ? a.residual : a.y;
+    const int64_t last4 = static_cast<int64_t>(a.N) * a.Co * plane - 4;
+    auto load_residual = [&](auto tiny) __attribute__((always_inline)) {
 #pragma unroll
-    for (int cf = 0; cf < WCO; ++cf) {
-      const int co = (cofrag0 + cf) * 16 + (lane & 15);
+      for (int cf = 0; cf < WCO; ++cf) {
+        const int co = (cofrag0 + cf) * 16 + (lane & 15);
 #pragma unroll
-      for (int pf = 0; pf < NPF; ++pf) {
-        const int h = h0 + wpx * WR + pf / WCF, w = w0 + (pf % WCF) * 16 + 4 * (lane >> 4);
-        const bool ok = has_r & (co < a.Co) & (h < a.H) & (w < a.W);
-        const int64_t off = (static_cast<int64_t>(n) * a.Co + (ok ? co : 0)) * plane +
-                            static_cast<int64_t>(o) * a.hw + (ok ? static_cast<int64_t>(h) * a.W + w : 0);
-        const uint16_t* rsrc = has_r ? a.residual + off : a.y;
-        if (ALIGNED) {
-          rv[cf][pf] = *reinterpret_cast<const uint2*>(rsrc);
-        } else if (ok & (w + 4 <= a.W)) {
-          __builtin_memcpy(&rv[cf][pf], rsrc, 8);  // at any 2-byte alignment
-        } else {
-          uint16_t e[4];
+        for (int pf = 0; pf < NPF; ++pf) {
+          const int h = h0 + wpx * WR + pf / WCF, w = w0 + (pf % WCF) * 16 + 4 * (lane >> 4);
+          const bool ok = has_r & (co < a.Co) & (h < a.H) & (w < a.W);
+          const int64_t off = ok ? (static_cast<int64_t>(n) * a.Co + co) * plane + static_cast<int64_t>(o) * a.hw +
+                                       static_cast<int64_t>(h) * a.W + w
+                                 : 0;
+          if constexpr (ALIGNED) {
+            rv[cf][pf] = *reinterpret_cast<const uint2*>(rsrc + off);
+          } else if constexpr (decltype(tiny)::value) {
+            uint16_t e[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) e[r] = rsrc[ok & (w + r < a.W) ? r : 0];
-          rv[cf][pf] = make_uint2(e[0] | (static_cast<uint32_t>(e[1]) << 16), e[2] | (static_cast<uint32_t>(e[3]) << 16));
+            for (int r = 0; r < 4; ++r) e[r] = rsrc[ok & (w + r < a.W) ? off + r : 0];
+            rv[cf][pf] = make_uint2(e[0] | (static_cast<uint32_t>(e[1]) << 16), e[2] | (static_cast<uint32_t>(e[3]) << 16));
+          } else {
+            const int64_t at = off < last4 ? off : last4;
+            uint64_t v;
+            __builtin_memcpy(&v, rsrc + at, 8);
+            v >>= 16 * static_cast<uint32_t>(off - at);
+            rv[cf][pf] = make_uint2(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32));
+          }
         }
       }
-    }
+    };
+    if (ALIGNED || last4 >= 0) load_residual(std::false_type{});
+    else load_residual(std::true_type{});
   }
 #pragma unroll
   for (int cf = 0; cf < WCO; ++cf) {
@@ -1084,8 +1099,8 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
   // A prologue in the kernel over unaligned tensors keeps the 96-channel tile:
   // a 32- or 48-channel one stages 320 segments with 256 threads, so that every
   // thread shifts, activates and masks two, and its registers overflow to
-  // scratch memory (160 -> 40 at 224x277, four frames: 1.062 ms, 0.311 on the
-  // 96-channel tile; 32 -> 48 at 87x171: 0.090, 0.040).
+  // scratch memory (160 -> 40 at 224x277, four frames: 1.062 ms, 0.326 on the
+  // 96-channel tile; 32 -> 48 at 87x171: 0.090, 0.036).
   const bool by_channels = fused == 2 && !aligned && g.d.Co <= 48;
   Plan pl = plan_bf16(g, by_channels);
   // split-K only with a large enough, 16-byte-aligned workspace; else unsplit

@@ -90,6 +90,28 @@ def test_odd_addresses_under_split_k(form):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), offset
 
 
+# an unaligned residual is read four elements at a time, the tensor's last ones
+# from its last four, and one by one where it has fewer than four
+@pytest.mark.parametrize("N,Co,T,H,W", [(1, 1, 1, 1, 1), (1, 1, 1, 1, 3), (3, 1, 1, 1, 1), (1, 2, 1, 1, 2),
+                                        (1, 1, 1, 1, 5), (1, 1, 1, 3, 3), (2, 17, 2, 5, 7), (1, 50, 1, 7, 66),
+                                        (1, 180, 1, 4, 67)])
+def test_unaligned_residual_to_its_last_element(N, Co, T, H, W):
+    sp = spec(N=N, Ci=8, Co=Co, T=T, Tc=2, H=H, W=W)
+    say(f"unaligned residual case {sp}")
+    w, b = layer(sp, "bf16", 917)
+    x, cache = chunk(sp, "bf16", 917, 0, 0), chunk(dict(sp, T=2), "bf16", 917, 0, 1)
+    shape = (N, Co) + c3c.output_dims(sp, "bf16")[:3]
+    # NaN on both sides: a value from outside the tensor would show
+    res = _at(inputs.residual_input(shape, "bf16", 917, 0, 0, "cuda"), 3)
+    ctx = c3c.Context(c3c.MODE_STRICT)
+    y, ybuf = guarded(shape, "bf16")
+    c3c.conv3d_causal_cached_fused(ctx, sp, x, cache, w, c3c.weight_repack(ctx, sp, w), b, None, None, res, y)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf), "a write outside the output"
+    ref, _ = oracle.conv3d_fused(sp, *oracle_args(sp, x, cache, w, b), None, None, res.cpu())
+    check(as_f64(y), ref, "bf16", str(sp))
+
+
 @pytest.mark.parametrize("over", [
     dict(Ci=40, Co=192, H=9, W=67), dict(Ci=33, Co=256, T=4, H=153, W=37), dict(Ci=31, Co=96, H=13, W=65),
     dict(Ci=40, Co=150, H=5, W=81), dict(N=2, Ci=35, Co=20, H=7, W=3), dict(Ci=256, Co=192, T=1, H=9, W=71),
