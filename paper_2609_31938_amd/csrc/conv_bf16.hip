@@ -852,27 +852,75 @@ namespace {
 
 int64_t compute_units() { return device_compute_units(); }
 
-// Whether a call of at most 48 output channels takes its own narrow tile
-// rather than the 96-channel one (the reason stands in plan_bf16).
-bool narrow_pays(const Geo& g, int64_t cus) {
-  Plan n, w;
-  set_tiles(g, 48, 8, 64, &n);  // one output-channel tile at 32 channels too
-  set_tiles(g, 96, 6, 64, &w);
-  return g.d.W % 8 != 0 || (n.blocks + cus - 1) / cus < (w.blocks + cus - 1) / cus;
+// Microseconds of one stage of a workgroup: its FLOP (2 * 288 * tile) at 6.9
+// TFLOP/s per compute unit, the measured main-loop rate.  A 32- or 48-channel
+// tile's time is its staging's, not its products': as a part of the 96-channel
+// tile's, 1.06 in aligned calls (400 -> 48 at 215x328, two frames, two rounds
+// each: 353 us, 333), 1.17 and 1.3 where the segments are shifted into place
+// (512 -> 32 at 170x301: 261, 218; 512 -> 48 at 49x105, two frames: 242, 189).
+double stage_time(const Geo& g, const Plan& p) {
+  const double flop = 2.0 * 9 * BKC / 6.9e6, wide = 96 * 6 * 64;
+  if (p.cfg == CFG_C32) return flop * wide * (g.d.W % 8 == 0 ? 1.06 : 1.17);
+  if (p.cfg == CFG_C48) return flop * wide * (g.d.W % 8 == 0 ? 1.06 : 1.3);
+  return flop * static_cast<double>(p.tile_flop_px);
 }
 
-// The tile configuration by output-channel count, and the split-K factor: a
-// call whose workgroups fill less than one round of the compute units splits
-// each tile's stages over S workgroups when the modelled time (microseconds)
-//   rounds(blocks * S) * (stages per split + 3) * t_stage
+// The split-K factor of a tiling: one whose workgroups fill less than one
+// round of the compute units splits each tile's stages over S workgroups when
+// the modelled time (microseconds)
+//   rounds(blocks * S) * (stages per split + 3) * stage_time
 //   + (S > 1) * (2 * S * output elements * 4 B / 5 TB/s + 5)
-// is lower than unsplit.  t_stage is one stage's FLOP (2 * 288 * tile) at
-// 6.9 TFLOP/s per compute unit, the measured main-loop rate; 3 stages stand
-// for a workgroup's fixed cost; the last term is the fp32 partial sums
-// written and read back, and the reduction launch.
-// by_channels: the tiling by output channels alone, without the rules that
-// take another one for its whole rounds of workgroups.
-Plan plan_bf16(const Geo& g, bool by_channels = false) {
+// is lower than unsplit.  3 stages stand for a workgroup's fixed cost; the
+// last term is the fp32 partial sums written and read back, and the reduction
+// launch.  Returns the modelled time (of less than one round; else 0).
+double split_k(const Geo& g, int64_t cus, Plan* p) {
+  p->splits = 1;
+  p->part_bytes = 0;
+  if (p->blocks <= 0 || p->blocks >= cus) return 0;
+  int64_t ntap = 0;  // most active taps of any output frame (Eq. 4)
+  for (int64_t o = 0; o < g.To; ++o) {
+    int64_t n = 0;
+    for (int64_t k = 0; k < g.d.Kt; ++k) {
+      const int64_t f = o + k * g.d.dil_t - g.p_l;
+      n += f >= 0 && f < g.Z;
+    }
+    ntap = n > ntap ? n : ntap;
+  }
+  const int64_t nst = ntap * ((g.d.Ci + BKC - 1) / BKC);
+  const double t_stage = stage_time(g, *p);
+  const int64_t out = g.d.N * g.d.Co * g.To * g.Ho * g.Wo;
+  auto cost = [&](int64_t S) {
+    const double rounds = static_cast<double>((p->blocks * S + cus - 1) / cus);
+    return rounds * static_cast<double>((nst + S - 1) / S + 3) * t_stage +
+           (S > 1 ? 2.0 * static_cast<double>(S) * static_cast<double>(out) * 4.0 / 5e6 + 5.0 : 0.0);
+  };
+  int64_t best = 1;
+  for (int64_t S = 2; S <= 8; ++S)
+    if (nst / S >= 4 && cost(S) < cost(best)) best = S;
+  p->splits = static_cast<int>(best);
+  if (best > 1) p->part_bytes = best * out * 4;
+  return cost(best);
+}
+
+// What a plan is made for.
+struct PlanFor {
+  bool by_channels = false;  // the tiling by output channels alone, without the
+                             // rules that take another for its rounds of workgroups
+  bool unsplit = false;      // no workspace for a split
+};
+
+// Whether a call of 17 to 48 output channels takes its own narrow tile n
+// rather than the 96-channel one w (the reason stands in plan_bf16).
+bool narrow_pays(const Geo& g, int64_t cus, Plan n, Plan w, const PlanFor& f) {
+  const int64_t rn = (n.blocks + cus - 1) / cus, rw = (w.blocks + cus - 1) / cus;
+  if (g.d.W % 8 == 0) return rn < rw;
+  if (f.unsplit || w.blocks >= cus)
+    return static_cast<double>(rn) * stage_time(g, n) < static_cast<double>(rw) * stage_time(g, w);
+  return split_k(g, cus, &n) < split_k(g, cus, &w);
+}
+
+// The tile configuration by output-channel count and the split-K factor.
+Plan plan_bf16(const Geo& g, const PlanFor& f = PlanFor{}) {
   Plan p;
   const int64_t Co = g.d.Co;
   const int64_t cus = compute_units();
@@ -885,24 +933,27 @@ Plan plan_bf16(const Geo& g, bool by_channels = false) {
     // 96-channel tile
     p.cfg = CFG_C16;
     set_tiles(g, 16, 8, 64, &p);
-  } else if (!by_channels && Co <= 48 && narrow_pays(g, cus)) {
-    // 32 or 48 channels x 8 x 64 pixels on four waves of 2 rows: a 96-channel
-    // tile would spend half or two thirds of its products on padding (1x3x3,
-    // 64 -> 32 at 533x610: 62 us against 49 here; the 48 -> 48 block form at
-    // 450x846, two frames: 419 against 374; 304 -> 48 at 107x210: 104 against
-    // 93).  A workgroup's time is its staging's, two rows more than the
-    // 96-channel tile's, so with no fewer rounds of workgroups and no unaligned
-    // loads to shift the wide tile stays (400 -> 48 at 215x328, two frames: 333
-    // against 353).  Above 48 a 64-channel tile of this shape would do as many products
-    // per LDS read and 12% fewer in all.
-    p.cfg = Co <= 32 ? CFG_C32 : CFG_C48;
-    set_tiles(g, Co <= 32 ? 32 : 48, 8, 64, &p);
   } else if (Co <= 96) {
     // 96 channels x 6 x 64 pixels on 2 x 2 waves (48 channels x 3 rows each):
     // each weight fragment is fetched by two waves, not four, and the smaller
     // halo tile leaves room for three LDS buffers
     p.cfg = CFG_C96;
     set_tiles(g, 96, 6, 64, &p);
+    // 32 or 48 channels x 8 x 64 pixels on four waves of 2 rows: a 96-channel
+    // tile would spend half or two thirds of its products on padding (1x3x3,
+    // 64 -> 32 at 533x610: 62 us against 49 here; the 48 -> 48 block form at
+    // 450x846, two frames: 419 against 374; 304 -> 48 at 107x210: 104 against
+    // 93).  Its workgroup stages two rows more, so aligned calls take it for
+    // fewer rounds of workgroups only, and odd widths, whose staging weighs
+    // more, by the modelled time, splits included (80 -> 40 at 171x181: 61 us,
+    // unsplit, against 39 on the wide tile in two; 464 -> 48 at 127x255 95
+    // against 131).
+    // Above 48 a 64-channel tile of this shape would do as many products per
+    // LDS read and 12% fewer in all.
+    Plan n;
+    n.cfg = Co <= 32 ? CFG_C32 : CFG_C48;
+    set_tiles(g, Co <= 32 ? 32 : 48, 8, 64, &n);
+    if (!f.by_channels && Co <= 48 && narrow_pays(g, cus, n, p, f)) p = n;
   } else {
     // 160-channel tiles of 4 x 80 or 10 x 32 pixels.  A workgroup of either
     // shape takes about the same time (measured), so the shape with fewer
@@ -937,7 +988,7 @@ Plan plan_bf16(const Geo& g, bool by_channels = false) {
     Plan r2;
     set_tiles(g, 128, 10, 32, &r2);
     const int64_t pco = p.cfg == CFG_C128_4X80 ? 128 : 160;
-    if (!by_channels && r2.tiles_co * 128 <= p.tiles_co * pco &&
+    if (!f.by_channels && r2.tiles_co * 128 <= p.tiles_co * pco &&
         ((r2.blocks + cus - 1) / cus) * 128 < ((p.blocks + cus - 1) / cus) * pco) {
       p = r2;
       p.cfg = CFG_C128_10X32;
@@ -948,38 +999,13 @@ Plan plan_bf16(const Geo& g, bool by_channels = false) {
     // 176 -> 176 at 352x640, two frames: 0.674, 0.875)
     Plan r3;
     set_tiles(g, 192, 4, 64, &r3);
-    if (!by_channels && r3.tiles_co * 192 < p.tiles_co * (p.tile_flop_px / 320) &&
+    if (!f.by_channels && r3.tiles_co * 192 < p.tiles_co * (p.tile_flop_px / 320) &&
         (r3.blocks + cus - 1) / cus * r3.tile_flop_px < (p.blocks + cus - 1) / cus * p.tile_flop_px) {
       p = r3;
       p.cfg = CFG_C192;
     }
   }
-  p.splits = 1;
-  p.part_bytes = 0;
-  if (p.blocks > 0 && p.blocks < cus) {
-    int64_t ntap = 0;  // most active taps of any output frame (Eq. 4)
-    for (int64_t o = 0; o < g.To; ++o) {
-      int64_t n = 0;
-      for (int64_t k = 0; k < g.d.Kt; ++k) {
-        const int64_t f = o + k * g.d.dil_t - g.p_l;
-        n += f >= 0 && f < g.Z;
-      }
-      ntap = n > ntap ? n : ntap;
-    }
-    const int64_t nst = ntap * ((g.d.Ci + BKC - 1) / BKC);
-    const double t_stage = 2.0 * 9 * BKC * static_cast<double>(p.tile_flop_px) / 6.9e6;
-    const double out_elems = static_cast<double>(g.d.N * Co * g.To * g.Ho * g.Wo);
-    auto cost = [&](int64_t S) {
-      const double rounds = static_cast<double>((p.blocks * S + cus - 1) / cus);
-      return rounds * static_cast<double>((nst + S - 1) / S + 3) * t_stage +
-             (S > 1 ? 2.0 * static_cast<double>(S) * out_elems * 4.0 / 5e6 + 5.0 : 0.0);
-    };
-    int64_t best = 1;
-    for (int64_t S = 2; S <= 8; ++S)
-      if (nst / S >= 4 && cost(S) < cost(best)) best = S;
-    p.splits = static_cast<int>(best);
-    if (best > 1) p.part_bytes = best * g.d.N * Co * g.To * g.Ho * g.Wo * 4;
-  }
+  split_k(g, cus, &p);
   return p;
 }
 
@@ -1046,7 +1072,7 @@ int64_t fast_bf16_workspace_bytes(const Geo& g) { return plan_bf16(g).part_bytes
 // the tiling by channels; 1018 -> 704, 4x3x3 taps at 95x90: 0.513, 0.472, 0.943).
 int64_t fast_bf16_noalloc_bytes(const Geo& g) {
   const int64_t need = plan_bf16(g).part_bytes;
-  return need > kNoallocScratchBytes && plan_bf16(g, true).part_bytes <= kNoallocScratchBytes ? 0 : need;
+  return need > kNoallocScratchBytes && plan_bf16(g, PlanFor{true}).part_bytes <= kNoallocScratchBytes ? 0 : need;
 }
 
 hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, const void* wpack,
@@ -1101,12 +1127,16 @@ hipError_t launch_fast_bf16(const Geo& g, const void* x, const void* cache, cons
   // thread shifts, activates and masks two, and its registers overflow to
   // scratch memory (160 -> 40 at 224x277, four frames: 1.062 ms, 0.326 on the
   // 96-channel tile; 32 -> 48 at 87x171: 0.090, 0.036).
-  const bool by_channels = fused == 2 && !aligned && g.d.Co <= 48;
-  Plan pl = plan_bf16(g, by_channels);
+  PlanFor f;
+  f.by_channels = fused == 2 && !aligned && g.d.Co <= 48;
+  Plan pl = plan_bf16(g, f);
   // split-K only with a large enough, 16-byte-aligned workspace; else unsplit
   const bool split = pl.splits > 1 && ws != nullptr && ws_bytes >= pl.part_bytes &&
                      (reinterpret_cast<uintptr_t>(ws) & 15u) == 0;
-  if (!split) pl = unsplit_plan(g, pl);
+  if (!split) {
+    f.unsplit = true;
+    pl = unsplit_plan(g, pl.splits > 1 && !g.channel_tiles ? plan_bf16(g, f) : pl);
+  }
   a.splits = split ? pl.splits : 1;
   a.part = split ? static_cast<float*>(ws) : nullptr;
   switch (pl.cfg) {

@@ -141,6 +141,17 @@ def test_odd_widths_match_the_oracle(over, ws):
     assert np.array_equal(got, oracle.cache_update(sp, "bf16", args[0], args[1]))
 
 
+@pytest.mark.parametrize("tile_co,splits,over", [(32, 1, dict(Ci=23, Co=20, T=2, H=195, W=263)),
+                                                 (48, 1, dict(Ci=23, Co=43, T=2, H=195, W=263)),
+                                                 (48, 4, dict(Ci=464, Co=41, T=1, H=127, W=255))])
+def test_odd_widths_on_the_narrow_tiles(tile_co, splits, over):
+    sp = spec(**dict(over, Tc=2))
+    need = c3c.workspace_bytes(sp, "bf16")
+    plan = c3c.plan_query(None, sp, "bf16", need)
+    assert (plan["tile_co"], plan["splits"]) == (tile_co, splits), plan
+    test_odd_widths_match_the_oracle(over, splits > 1)
+
+
 # the 1x1 kernels: 192 x 128-pixel tiles and the
 # 160 x 256 pointwise tiles, with ragged channels and pixel tiles, stride
 # 2, one source frame a tensor, new-cache frames in and out of the kernel

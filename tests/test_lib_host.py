@@ -482,6 +482,37 @@ def test_unsplit_calls_that_fill_few_compute_units_take_smaller_tiles():
 
 
 @no_gpu
+def test_narrow_tiles_where_they_take_less_time():
+    """17 to 48 output channels: aligned calls take the 32- or 48-channel tile
+    for fewer rounds of workgroups than the 96-channel one's; odd widths, whose
+    narrow stages take 1.17 and 1.3 of its time, by the modelled time with the
+    split that the workspace allows."""
+    def tile(Ci, Co, T, H, W, ws=True):
+        sp = spec(N=1, Ci=Ci, Co=Co, T=T, Tc=2, H=H, W=W)
+        pl = c3c.plan_query(None, sp, "bf16", c3c.workspace_bytes(sp, "bf16") if ws else 0)
+        return pl["tile_co"], pl["workgroups"], pl["splits"]
+    # aligned: 36 x 6 x 2 workgroups of 96 channels, 27 x 6 x 2 of 48, two rounds
+    # each; 330 of 96 channels against 250 of 32
+    assert tile(400, 48, 2, 215, 328) == (96, 432, 1)
+    assert tile(48, 32, 2, 195, 264) == (32, 250, 1)
+    # odd widths of one round: the wide tile, split or not
+    assert tile(352, 40, 1, 28, 55) == (96, 35, 7)
+    assert tile(560, 48, 1, 23, 27) == (96, 32, 8)
+    assert tile(160, 40, 1, 22, 29) == (96, 12, 3)
+    assert tile(160, 40, 1, 22, 29, False) == (96, 4, 1)
+    assert tile(80, 40, 1, 171, 181) == (96, 174, 2)
+    # ... but 64 narrow workgroups split four ways against 88 in two, and a
+    # narrow plan without its workspace is the wide one again
+    assert tile(464, 48, 1, 127, 255) == (48, 256, 4)
+    assert tile(464, 48, 1, 127, 255, False) == (96, 88, 1)
+    # fewer rounds: one against two; three of 1.17 against four
+    assert tile(48, 32, 2, 195, 263) == (32, 250, 1)
+    assert tile(48, 32, 3, 262, 263)[0] == 32
+    # as many rounds
+    assert tile(96, 48, 4, 172, 377)[0] == 96
+
+
+@no_gpu
 def test_head_kernel_takes_calls_whose_weight_table_fits():
     """The head kernel gathers its B operands into an LDS table of
     Kt x chunks x column-fragment entries (1 KiB each) beside its stage
