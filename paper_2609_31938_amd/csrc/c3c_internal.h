@@ -138,10 +138,13 @@ hipError_t launch_fast_tap1x1(const Geo& g, const void* x, const void* cache, co
 hipError_t launch_fallback(const Geo& g, const void* x, const void* cache, const void* w,
                            const void* bias, void* y, hipStream_t s, const Fuse& fu = Fuse{},
                            LaunchInfo* info = nullptr);
+// fallback, the direct kernel's workgroup (fallback.hip): output pixels, channels
+constexpr int kFallbackDirectPx = 512;
+constexpr int kFallbackDirectCo = 32;
 // fallback, bf16 / fp16 on matrix cores (fallback_mfma.hip).  False: the call
-// does not fit that kernel's tile (nothing launched, *err = hipSuccess) and
-// takes the direct kernel; true: launched, or described in *info, *err the
-// launch's status.
+// does not fit that kernel's tile, or has too few products for it (nothing
+// launched, *err = hipSuccess), and takes the direct kernel; true: launched,
+// or described in *info, *err the launch's status.
 bool launch_fallback_mfma(const Geo& g, const void* x, const void* cache, const void* w,
                           const void* bias, void* y, hipStream_t s, const Fuse& fu,
                           LaunchInfo* info, hipError_t* err);

@@ -7,7 +7,8 @@
 // right pad), and bf16 / fp16 / fp32 storage, accumulating in fp32.  Pointwise
 // (1x1x1) bf16 / fp16 calls go to the matrix-core kernel in pointwise.hip,
 // other bf16 / fp16 calls to the one in fallback_mfma.hip; the direct kernel
-// here keeps fp32 and the shapes whose windows do not fit that kernel's tile.
+// here keeps fp32, the shapes whose windows do not fit that kernel's tile, and
+// calls of so few products an output (depthwise ones) that it is the faster.
 #include "c3c_internal.h"
 #include "fuse_dev.h"
 
@@ -50,8 +51,8 @@ struct FbArgs {
 };
 
 constexpr int FB_THREADS = 256;
-constexpr int FB_PPT = 2;                         // output pixels per thread
-constexpr int FB_COB = 32;                        // output channels per workgroup
+constexpr int FB_PPT = kFallbackDirectPx / FB_THREADS;  // output pixels per thread
+constexpr int FB_COB = kFallbackDirectCo;         // output channels per workgroup
 constexpr int FB_WROW = FB_COB + 4;               // LDS floats per staged pair (padded)
 constexpr int FB_PAIRS = 224;                     // (input channel, tap) pairs per chunk
 constexpr int FB_U = 8;                           // pairs whose loads are in flight together

@@ -401,15 +401,44 @@ __global__ __launch_bounds__(256, 2) void fallback_mfma(FmArgs a) {
   }
 }
 
-// The tile of a call: output-channel configuration (index into the list
-// below), columns of pixel fragments, K per chunk.  False: the windows of a
-// 128-pixel tile do not fit LDS or the lane rounds (large strides, dilations
-// or kernels), or a size passes the kernel's 32-bit arithmetic: the direct
-// kernel takes the call.
 constexpr int FM_CFGS = 6;
 constexpr int FM_BCO[FM_CFGS] = {192, 128, 96, 64, 32, 16};
 
-bool pick(const Geo& g, FmArgs* a, int* cfg) {
+// Whether the direct kernel takes less time than blocks workgroups of the
+// 16-channel tile (the wider ones always win).  With few products an output
+// (a depthwise or thinly grouped call) a workgroup here does a 16 x 32 product
+// for a few useful ones and its time is its fixed cost, 1.42 us of a compute
+// unit for 128 pixels (0.36 more where planes are not aligned, 0.08 a tap in
+// time and a channel: the staging).  A direct one costs 2.2 us for 512 pixels,
+// 0.16 a product, 0.22 a source plane and 0.13 an output channel, and 2.5 +
+// 0.45 us a product from start to end, a quarter of which a full device still
+// shows.  Fitted to 1801 calls, 412 of which go to the direct kernel; on 24 the
+// faster kernel is more than 6% ahead of the one taken (1.25 at most).
+// Depthwise 1x3x3, 272 channels at 97x117, two frames: 89 us direct, 187 here;
+// 1x5x5, 280 channels at 23x44, four frames: 66 direct, 87 here; 3x3x3 at
+// stride 2, 512 channels at 151x328, four frames: 1690 direct, 1270 here.
+bool direct_pays(const Geo& g, int64_t Ktot, int64_t blocks, bool al) {
+  const c3c_conv_desc& d = g.d;
+  const int64_t cig = d.Ci / d.groups, cog = d.Co / d.groups;
+  const int64_t gy = d.groups * ((cog + kFallbackDirectCo - 1) / kFallbackDirectCo);
+  if (gy > 65535) return false;  // past the direct kernel's grid
+  const int64_t nb = gy * ((g.Ho * g.Wo + kFallbackDirectPx - 1) / kFallbackDirectPx) * g.To * d.N;
+  const double cus = static_cast<double>(device_compute_units()), k = static_cast<double>(Ktot);
+  const double here = static_cast<double>(blocks) / cus *
+                      ((al ? 1.42 : 1.78) + 0.08 * static_cast<double>(d.Kt - 1 + cig));
+  const double chain = 2.5 + 0.45 * k;
+  const double direct = chain / 4 + static_cast<double>(nb) / cus *
+                        (2.2 + 0.16 * k + 0.22 * static_cast<double>(cig * d.Kt) + 0.13 * static_cast<double>(cog));
+  return here > chain && here > direct;
+}
+
+// The tile of a call: output-channel configuration (index into the list
+// above), columns of pixel fragments, K per chunk.  False: the windows of a
+// 128-pixel tile do not fit LDS or the lane rounds (large strides, dilations
+// or kernels), a size passes the kernel's 32-bit arithmetic, or the products
+// are too few: the direct kernel takes the call.  al: planes aligned for
+// 16-byte loads.
+bool pick(const Geo& g, bool al, FmArgs* a, int* cfg) {
   const c3c_conv_desc& d = g.d;
   const int64_t lim = int64_t(1) << 29;
   for (int64_t v : {d.N, d.Ci, d.Co, d.T, d.Tc, d.H, d.W, g.To, g.Ho, g.Wo})
@@ -491,7 +520,7 @@ bool pick(const Geo& g, FmArgs* a, int* cfg) {
       blocks = nb;
     }
   }
-  if (blocks > 0x7fffffff) return false;
+  if (blocks > 0x7fffffff || (FM_BCO[*cfg] == 16 && direct_pays(g, Ktot, blocks, al))) return false;
   a->nblocks = static_cast<int>(blocks);
   a->groups = static_cast<int>(d.groups);
   a->cig = static_cast<int>(cig);
@@ -524,7 +553,8 @@ bool launch_fallback_mfma(const Geo& g, const void* x, const void* cache, const 
   FmArgs a{};
   int cfg = 0;
   *err = hipSuccess;
-  if (g.To < 1 || !pick(g, &a, &cfg)) return false;
+  const bool al = d.W % 8 == 0 && al16(x) && (cache == nullptr || al16(cache));
+  if (g.To < 1 || !pick(g, al, &a, &cfg)) return false;
   if (info) {
     info->kernel = C3C_KERNEL_FALLBACK_DIRECT;
     info->tile_co = FM_BCO[cfg];
@@ -555,7 +585,6 @@ bool launch_fallback_mfma(const Geo& g, const void* x, const void* cache, const 
   a.has_bias = d.has_bias ? 1 : 0;
   a.w_bytes = static_cast<uint32_t>(d.Co * a.Ktot * 2);
   a.w_al = al16(w) && a.Ktot % 8 == 0;
-  const bool al = d.W % 8 == 0 && al16(x) && (cache == nullptr || al16(cache));
   int64_t nch = a.kc % a.taps == 0 ? a.kc / a.taps : (a.kc + a.taps - 2) / a.taps + 1;
   if (nch > a.cig) nch = a.cig;
   const size_t lds = static_cast<size_t>(a.kc) * 4 + static_cast<size_t>(nch) * d.Kt * a.planep;

@@ -100,6 +100,9 @@ def test_every_output_channel_tile(Co, tile):
 @pytest.mark.parametrize("dtype,over", [
     ("bf16", dict(Ci=8, Co=8, T=1, H=200, W=300, Kt=1, s_h=40, s_w=40, p_h=1)),  # windows past LDS
     ("f32", dict(Ci=16, Co=24, T=2, H=20, W=31, Kt=1, s_h=2, s_w=2)),
+    # too few products an output: depthwise, and two channels a group
+    ("f16", dict(Ci=64, Co=64, T=2, H=97, W=117, Kt=1, groups=64)),
+    ("bf16", dict(Ci=64, Co=128, T=3, Tc=2, H=90, W=101, Kh=1, Kw=1, groups=32, s_h=2)),
 ])
 def test_direct_kernel_keeps_the_rest(dtype, over):
     plan, got, ref = _run(spec(**over), dtype, 0)

@@ -482,6 +482,26 @@ def test_unsplit_calls_that_fill_few_compute_units_take_smaller_tiles():
 
 
 @no_gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_calls_of_few_products_take_the_direct_fallback(dtype):
+    """A depthwise or thinly grouped call of enough workgroups runs on the direct
+    kernel (tile_h 0), which then takes less time than 16 x 32 products of a
+    few useful ones; small launches and groups of more products do not."""
+    def direct(**over):
+        pl = c3c.plan_query(None, spec(**over), dtype)
+        assert pl["kernel"] == "fallback_direct"
+        return pl["tile_h"] == 0
+    assert direct(Ci=272, Co=272, T=2, H=97, W=117, Kt=1, groups=272)
+    assert direct(Ci=192, Co=384, T=1, H=194, W=270, Kt=1, groups=192)
+    assert direct(Ci=328, Co=656, T=4, Tc=2, H=259, W=446, Kh=1, Kw=1, groups=328, s_h=2)
+    assert direct(Ci=136, Co=136, N=2, T=4, H=209, W=439, Kt=1, Kh=1, Kw=1, groups=68, s_h=2)
+    assert not direct(Ci=32, Co=32, T=1, H=20, W=24, Kt=1, groups=32)
+    assert not direct(Ci=304, Co=304, T=1, Tc=2, H=45, W=48, Kh=5, Kw=5, groups=304)
+    assert not direct(Ci=256, Co=256, T=4, Tc=2, H=60, W=104, groups=16)
+    assert not direct(Ci=192, Co=192, T=4, H=240, W=416, Kt=1, s_h=2, s_w=2)
+
+
+@no_gpu
 def test_narrow_tiles_where_they_take_less_time():
     """17 to 48 output channels: aligned calls take the 32- or 48-channel tile
     for fewer rounds of workgroups than the 96-channel one's; odd widths, whose
