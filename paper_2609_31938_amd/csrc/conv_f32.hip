@@ -393,12 +393,22 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
   // ms, 0.237 unsplit; 192 -> 192 at 60x104, four frames, 1200 workgroups:
   // 0.479, 0.462 unsplit).  Four waves were slower than two (0.25, 0.58 ms).
   const bool two = blocks <= 2 * device_compute_units();
+  // Few input channels: stages of 8 channels instead of 16 (32 for a 1x1
+  // kernel).  The larger stages' empty channels cost their loads into LDS, and
+  // the LDS they hold three workgroups of a compute unit at most: 3x1x1, 4 ->
+  // 284 at 141x267, four frames, 154 us against 89; 3x3x3, 3 -> 367 at 179x208,
+  // two batch elements, 189 against 136.  From 9 channels two stages a tap are
+  // the longer way for a 3x3 kernel (16 -> 16 at 85x84: 16.5 against 17.9), from
+  // 17 for a 1x1 one.
+  const bool thin = d.Ci <= (one ? 16 : 8);
   if (one) {
     if (small) launch_wk<1, 32, 1, 1, 4>(a, s);
+    else if (thin) launch_wk<1, 8, 2, 4, 1>(a, s);
     else if (two) launch_wk<1, 32, 2, 4, 2>(a, s);
     else launch_wk<1, 32, 2, 4, 1>(a, s);
   } else {
     if (small) launch_wk<3, 32, 1, 1, 4>(a, s);
+    else if (thin) launch_wk<3, 8, 4, 4, 1>(a, s);
     else if (two) launch_wk<3, 16, 4, 4, 2>(a, s);
     else launch_wk<3, 16, 4, 4, 1>(a, s);
   }

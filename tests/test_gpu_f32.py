@@ -48,7 +48,22 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("over", CASES)
+# few input channels: stages of 8, one to three of them
+THIN = [
+    dict(Ci=1, Co=33, T=2, Tc=2, H=12, W=40),
+    dict(Ci=2, Co=5, T=3, Tc=2, H=7, W=33, p_r=1),
+    dict(Ci=7, Co=64, T=2, Tc=1, H=21, W=19),
+    dict(N=2, Ci=8, Co=40, T=4, Tc=2, H=60, W=104),
+    dict(Ci=9, Co=20, T=2, Tc=2, H=9, W=21),
+    dict(Ci=1, Co=3, T=2, Tc=2, H=3, W=43, Kh=1, Kw=1),
+    dict(Ci=8, Co=70, T=2, Tc=2, H=11, W=129, Kh=1, Kw=1),
+    dict(N=2, Ci=9, Co=33, T=3, Tc=2, H=5, W=27, Kh=1, Kw=1),
+    dict(Ci=16, Co=40, T=9, Tc=1, H=40, W=104, Kh=1, Kw=1, s_t=2, p_base=1),
+    dict(Ci=17, Co=20, T=2, Tc=2, H=9, W=21, Kh=1, Kw=1),
+]
+
+
+@pytest.mark.parametrize("over", CASES + THIN)
 def test_f32_kernel_matches_oracle(over):
     sp = spec(**over)
     ctx = c3c.Context(c3c.MODE_STRICT)
@@ -70,7 +85,8 @@ def test_f32_kernel_matches_oracle(over):
     assert np.array_equal(host(co).numpy(), oracle.cache_update(sp, "f32", args[0], args[1]))
 
 
-@pytest.mark.parametrize("over", [dict(Ci=17, Co=20, H=9, W=21), dict(Ci=35, Co=20, H=9, W=21, Kh=1, Kw=1)])
+@pytest.mark.parametrize("over", [dict(Ci=17, Co=20, H=9, W=21), dict(Ci=35, Co=20, H=9, W=21, Kh=1, Kw=1),
+                                  dict(Ci=3, Co=20, H=9, W=21), dict(Ci=9, Co=20, H=9, W=21, Kh=1, Kw=1)])
 def test_infinity_stays_in_its_receptive_field(over):
     """Padding -- channel pairs past the last, lanes past the tile -- multiplies nothing."""
     sp = spec(T=2, Tc=2, **over)
