@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2609_31938_amd import c3c
+from paper_2609_31938_amd import c3c, inputs
 from paper_2609_31938_amd.inputs import spec
 
 from gpu_util import as_f64, chunk, guarded, guards_intact, layer, metrics, oracle_args, say
@@ -95,6 +95,67 @@ def test_every_output_channel_tile(Co, tile):
     assert plan["tile_co"] == tile, plan
     m = metrics(got, ref)
     assert m["nonfinite"] == 0 and m["rel"] <= BAR["f16" if even else "bf16"], m
+
+
+# Every wide tile with K in several chunks and a ragged last one (1350 and 1620
+# products; a chunk has at most 1152): the weights carried from one chunk to the
+# next, the windows staged again, several passes of the staging loop; and three
+# taps in time with frames outside Z on both sides.
+@pytest.mark.parametrize("Co,tile", [(190, 192), (125, 128), (90, 96), (64, 64), (30, 32)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("odd", [False, True])
+@pytest.mark.parametrize("over", [dict(Ci=150, T=4, Kt=1), dict(Ci=60, T=2, Tc=1, p_base=3, p_r=1)])
+def test_wide_tiles_over_several_chunks(Co, tile, dtype, odd, over):
+    sp = spec(Co=Co, H=160, W=321 if odd else 320, s_h=2, s_w=2, **over)
+    plan = c3c.plan_query(None, sp, dtype)
+    say(f"fallback case {dtype} {sp} odd={odd} plan={plan}")
+    assert (plan["kernel"], plan["tile_co"]) == ("fallback_direct", tile) and plan["tile_h"] > 0, plan
+    w, b = layer(sp, dtype, 913)
+    x = chunk(sp, dtype, 913, 0, 0)
+    cache = chunk(dict(sp, T=sp["Tc"]), dtype, 913, 0, 1) if sp["Tc"] else None
+    args = oracle_args(sp, x, cache, w, b)
+    if odd:
+        w, x, cache = _odd(w), _odd(x), None if cache is None else _odd(cache)
+    To, Ho, Wo, L = c3c.output_dims(sp, dtype)
+    y, ybuf = guarded((1, Co, To, Ho, Wo), dtype)
+    c3c.conv3d_causal_cached(c3c.Context(), sp, x, cache, w, None, b, y, None)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf), "a write outside the output"
+    assert torch.isfinite(y).all()
+    # whole planes: the tile's first, last and middle channels, every frame
+    for t in range(To):
+        for co in sorted({0, 15, 16, Co // 2, Co - 1}):
+            r0 = (co * To + t) * Ho
+            ref = oracle.conv3d_rows(sp, dtype, *args, r0, r0 + Ho)
+            m = metrics(as_f64(y[0, co, t]), ref)
+            assert m["rel"] <= BAR[dtype], (t, co, m)
+
+
+@pytest.mark.parametrize("Co,tile", [(190, 192), (64, 64)])
+@pytest.mark.parametrize("odd", [False, True])
+def test_fused_form_on_the_wide_tiles(Co, tile, odd):
+    """The prologue applied while a chunk's windows are staged (several passes of
+    the staging loop), and the residual."""
+    sp = spec(Ci=150, Co=Co, T=4, H=160, W=321 if odd else 320, Kt=1, s_h=2, s_w=2)
+    assert c3c.plan_query(None, sp, "bf16")["tile_co"] == tile
+    say(f"fallback case fused {sp} odd={odd}")
+    w, b = layer(sp, "bf16", 913)
+    x = chunk(sp, "bf16", 913, 0, 0)
+    scale, shift = inputs.affine_inputs(sp, 913, 0, 0, "cuda")
+    To, Ho, Wo, _ = c3c.output_dims(sp, "bf16")
+    res = inputs.residual_input((1, Co, To, Ho, Wo), "bf16", 913, 0, 0, "cuda")
+    u = oracle.prologue_bf16(sp, x.cpu(), scale.cpu(), shift.cpu())
+    y, ybuf = guarded((1, Co, To, Ho, Wo), "bf16")
+    c3c.conv3d_causal_cached_fused(c3c.Context(), sp, _odd(x) if odd else x, None, w, None, b, scale, shift,
+                                   _odd(res) if odd else res, y)
+    torch.cuda.synchronize()
+    assert guards_intact(ybuf) and torch.isfinite(y).all()
+    for t in (0, To - 1):
+        for co in (0, 17, Co - 1):
+            r0 = (co * To + t) * Ho
+            ref = oracle.conv3d_rows(sp, "bf16", u, None, w.cpu(), b.cpu(), r0, r0 + Ho) + as_f64(res[0, co, t])
+            m = metrics(as_f64(y[0, co, t]), ref)
+            assert m["rel"] <= BAR["bf16"], (t, co, m)
 
 
 @pytest.mark.parametrize("dtype,over", [
