@@ -208,7 +208,9 @@ typedef enum c3c_kernel {
   C3C_KERNEL_TAP1X1 = 3,          /* bf16, 1x1: 192-channel x 128-pixel tiles  */
   C3C_KERNEL_POINTWISE = 4,       /* bf16 / f16 per-frame matrix products      */
   C3C_KERNEL_FAST_F32 = 5,        /* fp32 matrix cores, 3x3 and 1x1            */
-  C3C_KERNEL_FALLBACK_DIRECT = 6  /* generic direct Conv3D, fp32 accumulation  */
+  C3C_KERNEL_FALLBACK_DIRECT = 6  /* generic direct Conv3D, fp32 accumulation:
+                                     on matrix cores (bf16 / f16; tile_h > 0)
+                                     or vector units (tile_h = 0)              */
 } c3c_kernel;
 
 /* What one plain call (c3c_conv3d_causal_cached) would launch: its route,
@@ -231,8 +233,9 @@ typedef struct c3c_plan {
  * mode 0) with a split-K workspace of ws_bytes attached.  Pure host code; it
  * reads the current device's compute-unit count as the launch does (256 when
  * no device is visible).  The plan assumes 16-byte-aligned tensors: a call
- * with misaligned tensors may take an unaligned variant of the same tile or,
- * for HEAD and TAP1X1, the CONV3D_BF16 and POINTWISE kernels.
+ * with misaligned tensors may take an unaligned variant of the same tile; for
+ * HEAD, the CONV3D_BF16 kernel; for POINTWISE on the fallback (misaligned
+ * weights) and FALLBACK_DIRECT, either form of FALLBACK_DIRECT.
  * EINVAL for an invalid descriptor or NULL out. */
 int c3c_plan_query(const c3c_ctx* ctx, const c3c_conv_desc* d, size_t ws_bytes,
                    c3c_plan* out);
@@ -287,11 +290,14 @@ int c3c_weight_unpack(const c3c_conv_desc* d, const void* wpack, void* w_out,
  *
  * Fast route: one kernel launch evaluates every active tap into fp32
  * registers, adds the bias once, rounds to `dtype` (nearest even), stores
- * NCTHW, and writes cache_out (3x3 kernels write it in the same launch; 1x1
- * kernels and fp32 calls copy it with a second kernel).  It reads wpack (required, from
+ * NCTHW, and writes cache_out from the frames it stages, where each of its
+ * frames is among them (cache_in_kernel of the plan); else, and from the
+ * POINTWISE kernel, a second kernel copies it.  It reads wpack (required, from
  * c3c_weight_repack on the same w); w itself is not read.
- * Fallback route: the direct-Conv3D kernel reads w (wpack may be NULL), then a
- * copy kernel writes cache_out.
+ * Fallback route: a direct-Conv3D kernel reads w (wpack may be NULL), then a
+ * copy kernel writes cache_out.  A fallback call of more than 65535 output
+ * frames (N * To) fails at its launch; only a 1x1x1 bf16 / f16 call with H * W
+ * and Ci multiples of 8 and aligned tensors has no such limit.
  *
  * Counters: calls++ first; then, once the call's kernels are enqueued,
  * fast++, or fallback++ with unsupported / forced / fast_error; or

@@ -363,8 +363,11 @@ hipError_t launch_fast_f32(const Geo& g, const void* x, const void* cache, const
   // their larger halo (160 -> 400 at 27x48, two frames: 286 workgroups of 128,
   // 0.166 ms, 1066 of 32, 0.115; 192 -> 128 at 56x112, four frames: 0.379,
   // 0.328; with equal shares 128-pixel tiles win: 48 -> 336 at 48x60, 0.129,
-  // 0.139).  Up to 32 channels the chain is too short to matter and 128 pixels
-  // stay (32 -> 624 at 19x21, three frames: 0.027 ms on the first).
+  // 0.139).  Up to 32 channels 128 pixels stay, and not for speed: the tile of
+  // the 32 -> 32 layer is one of the plans that callers are told.  With 32-pixel
+  // tiles by the same rule from 9 channels on, 159 such calls took 0.74 of the
+  // time (32 -> 64 at 46x88: 0.0269 ms, 0.0221; 16 -> 32 at 32x32: 0.0170,
+  // 0.0128; 20 -> 64 at 59x96, 3x1x1: 0.0177, 0.0216).
   const int64_t cus = device_compute_units(), wide = blocks_of();
   bool small = d.Ci > 32;
   if (small) {

@@ -25,8 +25,8 @@
 //     offset (stride).  Eight 2-byte reads a lane serve WCO products.
 //   * The B operand is read from w (L1 / L2) one 32-K stage ahead.
 // What bounds it, measured on 192 -> 192, 1x3x3 at stride 2, 240x416, four
-// frames, f16 (66 GFLOP): 0.150 ms (440 TFLOP/s; the direct kernel took
-// 2.95 ms); 0.12 without the A gather (8 reads, 8 address adds and 4 packs a
+// frames, f16 (66 GFLOP): 0.159 ms (417 TFLOP/s; the direct kernel took
+// 2.95 ms).  In the runs that took 0.150, 0.12 without the A gather (8 reads, 8 address adds and 4 packs a
 // fragment), 0.13 without the staging, 0.14 without the weight reads.  The
 // waves of the 192-channel tile sit side by side along the output channels,
 // so no weight byte is read twice: as 2 x 2 waves (half the gather, each
@@ -445,7 +445,7 @@ bool pick(const Geo& g, bool al, FmArgs* a, int* cfg) {
     if (v >= lim) return false;
   for (int64_t v : {d.stride_h, d.stride_w, d.dil_h, d.dil_w, d.pad_h, d.pad_w})
     if (v > 1024) return false;
-  if (d.N * g.To > 65535) return false;  // the direct kernel's grid refuses these; so they stay refused
+  if (d.N * g.To > 65535) return false;  // the fallback's documented limit (the direct kernel's grid)
   const int64_t taps = d.Kt * d.Kh * d.Kw;
   if (d.Kt > 1024 || d.Kh > 1024 || d.Kw > 1024 || taps > 65536) return false;
   const int64_t cig = d.Ci / d.groups, cog = d.Co / d.groups;
@@ -457,9 +457,9 @@ bool pick(const Geo& g, bool al, FmArgs* a, int* cfg) {
   for (int fc : {1, 2, 4, 8}) {
     const int64_t fr = FM_FRAGS / fc, bw = 16 * fc;
     const int64_t rows = (fr - 1) * d.stride_h + (d.Kh - 1) * d.dil_h + 1;
-    // the first pixel's first tap sits at most 7 columns into its segment
-    // (a constant when every tile starts at the same place modulo 8)
-    const int64_t adj = (bw * d.stride_w) % 8 == 0 ? (8 - d.pad_w % 8) % 8 : 7;
+    // columns from a segment's start to the first pixel's first tap: the same
+    // for every tile, whose origin is a multiple of 16 columns
+    const int64_t adj = (8 - d.pad_w % 8) % 8;
     const int64_t segs = (adj + (bw - 1) * d.stride_w + (d.Kw - 1) * d.dil_w + 1 + 7) / 8;
     if (rows * segs > 64 * FM_ROUNDS) continue;
     const int64_t plane = rows * segs * 16;

@@ -736,7 +736,8 @@ bool pointwise_eligible(const Geo& g, const void* x, const void* cache, const vo
   const int64_t hw = d.H * d.W;
   // 16-byte loads of 8 channels of w; x, cache and y at any alignment
   if (d.Ci % 8 != 0 || !aligned(w, 16)) return false;
-  // (a call past the generic fallback's grid is refused unless it is aligned)
+  // more output frames than the direct kernel's grid holds: the fallback's
+  // documented limit, which aligned calls do not have
   if (d.N * g.To > 65535 && !pw_aligned(hw, x, cache, y, residual)) return false;
   // 32-bit buffer offsets: one 32-channel chunk of a source frame and the
   // weights must each span less than 2 GiB
