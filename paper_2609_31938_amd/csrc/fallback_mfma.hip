@@ -407,16 +407,16 @@ constexpr int FM_BCO[FM_CFGS] = {192, 128, 96, 64, 32, 16};
 // Whether the direct kernel takes less time than blocks workgroups of the
 // 16-channel tile (the wider ones always win).  With few products an output
 // (a depthwise or thinly grouped call) a workgroup here does a 16 x 32 product
-// for a few useful ones and its time is its fixed cost, 1.42 us of a compute
-// unit for 128 pixels (0.36 more where planes are not aligned, 0.08 a tap in
-// time and a channel: the staging).  A direct one costs 2.2 us for 512 pixels,
-// 0.16 a product, 0.22 a source plane and 0.13 an output channel, and 2.5 +
-// 0.45 us a product from start to end, a quarter of which a full device still
-// shows.  Fitted to 1801 calls, 412 of which go to the direct kernel; on 24 the
-// faster kernel is more than 6% ahead of the one taken (1.25 at most).
-// Depthwise 1x3x3, 272 channels at 97x117, two frames: 89 us direct, 187 here;
-// 1x5x5, 280 channels at 23x44, four frames: 66 direct, 87 here; 3x3x3 at
-// stride 2, 512 channels at 151x328, four frames: 1690 direct, 1270 here.
+// for a few useful ones and its time is its fixed cost, 1.49 us of a compute
+// unit for 128 pixels (0.42 more where planes are not aligned, 0.07 a staged
+// source plane).  A direct one costs 1.88 us for 512 pixels, 0.18 a product,
+// 0.26 a source plane and 0.135 an output channel, and 3.6 + 0.6 us a product
+// from start to end, a fifth of which a full device still shows.  Fitted to
+// 2489 calls, 591 of which go to the direct kernel; on 35 the faster kernel is
+// more than 6% ahead of the one taken (1.25 at most).  Depthwise 1x3x3, 272
+// channels at 97x117, two frames: 89 us direct, 187 here; 1x5x5, 280 channels
+// at 23x44, four frames: 66 direct, 87 here; 3x3x3 at stride 2, 512 channels at
+// 151x328, four frames: 1690 direct, 1270 here.
 bool direct_pays(const Geo& g, int64_t Ktot, int64_t blocks, bool al) {
   const c3c_conv_desc& d = g.d;
   const int64_t cig = d.Ci / d.groups, cog = d.Co / d.groups;
@@ -424,11 +424,11 @@ bool direct_pays(const Geo& g, int64_t Ktot, int64_t blocks, bool al) {
   if (gy > 65535) return false;  // past the direct kernel's grid
   const int64_t nb = gy * ((g.Ho * g.Wo + kFallbackDirectPx - 1) / kFallbackDirectPx) * g.To * d.N;
   const double cus = static_cast<double>(device_compute_units()), k = static_cast<double>(Ktot);
-  const double here = static_cast<double>(blocks) / cus *
-                      ((al ? 1.42 : 1.78) + 0.08 * static_cast<double>(d.Kt - 1 + cig));
-  const double chain = 2.5 + 0.45 * k;
-  const double direct = chain / 4 + static_cast<double>(nb) / cus *
-                        (2.2 + 0.16 * k + 0.22 * static_cast<double>(cig * d.Kt) + 0.13 * static_cast<double>(cog));
+  const double planes = static_cast<double>(cig * d.Kt);
+  const double here = static_cast<double>(blocks) / cus * ((al ? 1.49 : 1.91) + 0.07 * planes);
+  const double chain = 3.6 + 0.6 * k;
+  const double direct = 0.22 * chain + static_cast<double>(nb) / cus *
+                        (1.88 + 0.18 * k + 0.26 * planes + 0.135 * static_cast<double>(cog));
   return here > chain && here > direct;
 }
 
