@@ -1,6 +1,6 @@
 """GPU parity of the fp32 kernel against the oracle where its tiling can go
 wrong: narrow, flat and odd frames (the tile's shape follows the frame),
-channel counts around a stage (16 channels; 32 for 1x1), odd channel pairs,
+channel counts around a stage (8, 16 or 32 channels), odd channel pairs,
 ragged output-channel tiles, both wave splits, frames outside Z, the cache
 written by the kernel and by the copy.
 
